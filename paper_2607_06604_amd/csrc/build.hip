@@ -638,6 +638,7 @@ void build_begin(Ctx &ctx, Graph &g, const double *xyz, const double *w, BuildJo
     // wrap and takes any count
     int nc = g.periodic ? (ncd < 3 ? 1 : (int)ncd) : std::max(1, (int)ncd);
     uint64_t ncell = (uint64_t)nc * nc * nc;
+    g.cell_points = (double)n / (double)ncell;
 
     const std::shared_ptr<DevPool> &pool = ctx.pool;
     DevBuf cell_of(sizeof(uint32_t) * n, pool), count(sizeof(uint32_t) * ncell, pool),

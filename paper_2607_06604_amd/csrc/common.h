@@ -195,6 +195,7 @@ struct Graph {
     int wscale = 0;           // exact-sum scale of weighted triangles (kNoScale: none)
     double wmin = 0, wmax = 0;  // smallest and largest weight magnitude
     bool wneg = false;          // some weight is negative
+    double cell_points = 0;     // mean points per cell of the build's grid
     Bins bins;
     uint64_t pair_hist[255] = {};
     uint64_t sum_sq_deg = 0;  // sum over points of (full degree)^2
@@ -343,6 +344,7 @@ void build_end(Ctx &ctx, Graph &g, BuildJob &job, bool tile_ok);
 struct Batch3 {
     DevBuf dv;          // device results + queues
     DevBuf gd;          // descriptors
+    DevBuf rows;        // (unused by unweighted counts)
     HostBuf hostdesc;   // staging of descriptors
     HostBuf hostcfg;    // staging of the configuration table
     HostBuf out;        // pinned results

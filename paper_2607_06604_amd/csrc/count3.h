@@ -1,0 +1,115 @@
+// count3.h - what the two triangle-count kernels (hash table: count3.hip,
+// paged table: count3p.hip) and their launch code share.
+#pragma once
+
+#include "kern_util.h"
+
+namespace gsn {
+
+// One catalogue of a batched launch: its forward CSR, its first virtual hub
+// index and where its counts go.
+struct GDesc {
+    const uint64_t *rp;
+    const uint32_t *col;
+    const uint8_t *bin;
+    uint64_t v0;              // virtual hub index of label 0
+    uint32_t n;
+    uint32_t pad;
+    unsigned long long *hist; // nconf
+    unsigned long long *ntri; // 1
+};
+
+struct C3Args {
+    const GDesc *gd;        // batched launch: ngraph descriptors (else null)
+    int ngraph;
+    uint32_t nvirt;         // batched launch: total hubs over all catalogues
+    const uint64_t *rp;
+    const uint32_t *hcol;   // hub rows (entry e of row i at rp[i] - hbase + e)
+    const uint8_t *hbin;
+    const uint32_t *scol;   // spoke rows (row j at rp[j] - sbase)
+    const uint8_t *sbin;
+    uint64_t hbase, sbase;
+    uint32_t h0, h1, s0, s1;
+    const double *w;        // label-ordered weights (weighted)
+    const uint32_t *perm;   // label -> original index (anchored)
+    const uint8_t *mark;    // anchored: hubs that can own an anchored triangle (nullable)
+    int nb, nconf, log2h;
+    int trunc;              // cut spoke rows at the hub row's largest label
+    int packed;             // hash entries hold (bin << 24 | label): labels < 2^24 - 1
+    int glog;               // entries per step = 2^glog
+    int mode;               // hit counter addressing: kRank, kLut or kCube
+    int kmax;               // hubs per group (1..kMaxGroup)
+    int yshift;             // packed hash entries: bin << yshift | hub << 24 | label
+    uint64_t group_cap;     // rows of a group (beyond the first hub) fit this many entries
+    uint32_t maxdeg;
+    uint32_t tmax;          // steps per table fill
+    uint32_t tcap;          // table entries: tmax + padding of one pass
+    int inorder;            // paged table: hubs handed out one at a time in label order, device-wide
+    uint32_t tbytes;        // paged table: bytes of its pages (the zero page among them)
+    double *wrow;           // paged table, long rows: packed weights and original indices of a
+    uint32_t *prow;         // work group's hub row, maxdeg entries each
+    uint32_t rowgroups;     // work groups they serve
+    uint32_t anchor_lo, anchor_hi;
+    double wmul;            // 2^wscale
+    int wgen;               // some weight is negative or some term may reach 2^63
+    uint64_t flush_limit;   // flush LDS counters before this many increments
+    int refresh;            // paged table: bound the fullest counter by reading it before a flush
+    uint32_t *queue;        // kQueueWords words
+    unsigned long long *hist;   // nconf
+    unsigned long long *wsum;   // 2*nconf (lo, hi)
+    unsigned long long *ntri;   // 1
+    unsigned long long *probes; // candidates probed (nullable)
+    uint32_t *err;          // bit 1: LDS addressing
+    uint64_t wspan;         // WIDE: entries a segment of spoke rows may span from its first row
+    const uint16_t *cfg3;   // kLut / kCube: configuration index of ordered triple (x*nb + y)*nb + z
+    const uint32_t *tiles;  // hub tiles of about equal cost: tile t = [tiles[t], tiles[t+1]) (or null)
+    uint32_t ntiles;
+};
+
+constexpr int kLutMaxBins = 24;          // nb^3 u16 table up to 27 KB
+constexpr int kCubeMaxBins = 16;         // nb^3 u32 counters up to 16 KB
+constexpr int kMaxGroup = 4;             // hubs per group: two bits in a step entry
+
+// How a hit finds its counter: the configuration index from the rank tables
+// (kRank), an nb^3 table of counter addresses (kLut), or no index at all --
+// one LDS counter per ordered bin triple (x, y, z), folded into
+// configurations when the counters are flushed (kCube, unweighted only).
+enum { kRank = 0, kLut = 1, kCube = 2 };
+
+// The schedule of a paged-table count (count3p.hip).
+struct PlanP {
+    int block = 256;
+    int glog = 4;          // entries per step = 2^glog (4 to 6)
+    int mode = kLut;
+    int kmax = kMaxGroup;  // hubs per group at most
+    uint32_t tbytes = 0;   // bytes of the label table's pages
+    uint32_t lds = 0;
+};
+
+// The schedule for a graph of the given degrees, or false where the paged
+// table does not serve (then the hash table does).
+bool planp(const Ctx &ctx, uint32_t maxdeg, int nb, bool weighted, bool anchored, uint64_t n, double mean_row,
+           double cell_points, const Tune3 &tune, PlanP &p);
+// rows: device memory the launch may need (taken on first use; held by the
+// caller until the launch has completed).
+void launchp(Ctx &ctx, hipStream_t s, const C3Args &a, const PlanP &P, bool weighted, bool anchored, bool batch,
+             bool wide, DevBuf &rows);
+
+// Catalogue of virtual hub v: the last descriptor with v0 <= v.
+__device__ __forceinline__ int graph_of(const GDesc *gd, int ng, uint32_t v) {
+    int lo = 0, hi = ng;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (gd[mid].v0 <= v) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+__device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+}  // namespace gsn

@@ -26,64 +26,10 @@
 #include <cstdlib>
 #include <cstring>
 
-#include "kern_util.h"
+#include "count3.h"
 
 namespace gsn {
 namespace {
-
-// One catalogue of a batched launch: its forward CSR, its first virtual hub
-// index and where its counts go.
-struct GDesc {
-    const uint64_t *rp;
-    const uint32_t *col;
-    const uint8_t *bin;
-    uint64_t v0;              // virtual hub index of label 0
-    uint32_t n;
-    uint32_t pad;
-    unsigned long long *hist; // nconf
-    unsigned long long *ntri; // 1
-};
-
-struct C3Args {
-    const GDesc *gd;        // batched launch: ngraph descriptors (else null)
-    int ngraph;
-    uint32_t nvirt;         // batched launch: total hubs over all catalogues
-    const uint64_t *rp;
-    const uint32_t *hcol;   // hub rows (entry e of row i at rp[i] - hbase + e)
-    const uint8_t *hbin;
-    const uint32_t *scol;   // spoke rows (row j at rp[j] - sbase)
-    const uint8_t *sbin;
-    uint64_t hbase, sbase;
-    uint32_t h0, h1, s0, s1;
-    const double *w;        // label-ordered weights (weighted)
-    const uint32_t *perm;   // label -> original index (anchored)
-    const uint8_t *mark;    // anchored: hubs that can own an anchored triangle (nullable)
-    int nb, nconf, log2h;
-    int trunc;              // cut spoke rows at the hub row's largest label
-    int packed;             // hash entries hold (bin << 24 | label): labels < 2^24 - 1
-    int glog;               // entries per step = 2^glog
-    int mode;               // hit counter addressing: kRank, kLut or kCube
-    int kmax;               // hubs per group (1..kMaxGroup)
-    int yshift;             // packed hash entries: bin << yshift | hub << 24 | label
-    uint64_t group_cap;     // rows of a group (beyond the first hub) fit this many entries
-    uint32_t maxdeg;
-    uint32_t tmax;          // steps per table fill
-    uint32_t tcap;          // table entries: tmax + padding of one pass
-    uint32_t anchor_lo, anchor_hi;
-    double wmul;            // 2^wscale
-    int wgen;               // some weight is negative or some term may reach 2^63
-    uint64_t flush_limit;   // flush LDS counters before this many increments
-    uint32_t *queue;        // kQueueWords words
-    unsigned long long *hist;   // nconf
-    unsigned long long *wsum;   // 2*nconf (lo, hi)
-    unsigned long long *ntri;   // 1
-    unsigned long long *probes; // candidates probed (nullable)
-    uint32_t *err;          // bit 1: LDS addressing
-    uint64_t wspan;         // WIDE: entries a segment of spoke rows may span from its first row
-    const uint16_t *cfg3;   // kLut / kCube: configuration index of ordered triple (x*nb + y)*nb + z
-    const uint32_t *tiles;  // hub tiles of about equal cost: tile t = [tiles[t], tiles[t+1]) (or null)
-    uint32_t ntiles;
-};
 
 constexpr int kUnroll3 = 4;              // steps per lane per pass
 // Weighted unanchored counts (six wavefronts per SIMD at most: their LDS
@@ -94,15 +40,6 @@ constexpr int kUnroll3W = 6;
 __host__ __device__ constexpr int unroll3(bool weighted, bool anchored) {
     return weighted && !anchored ? kUnroll3W : kUnroll3;
 }
-constexpr int kLutMaxBins = 24;          // nb^3 u16 table up to 27 KB
-constexpr int kCubeMaxBins = 16;         // nb^3 u32 counters up to 16 KB
-constexpr int kMaxGroup = 4;             // hubs per group: two bits in a step entry
-
-// How a hit finds its counter: the configuration index from the rank tables
-// (kRank), an nb^3 table of counter addresses (kLut), or no index at all --
-// one LDS counter per ordered bin triple (x, y, z), folded into
-// configurations when the counters are flushed (kCube, unweighted only).
-enum { kRank = 0, kLut = 1, kCube = 2 };
 // Spoke rows of one hub are addressed by 32-bit offsets from the hub's
 // first spoke row: byte offsets (loads with a scalar base) below 2^30
 // entries, entry offsets with 64-bit addresses (WIDE launches) below 2^32.
@@ -156,12 +93,6 @@ __device__ __forceinline__ uint32_t hub_hash(uint32_t k, int log2h) {
 }
 
 
-__device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // Move the LDS counters into the 64-bit results (and their sum into the
 // triangle total); the caller brackets it with barriers.
 template <int BLOCK, bool WEIGHTED, bool LDS_HIST>
@@ -206,17 +137,6 @@ __device__ void flush3(const C3Args &a, const Layout3 &L, unsigned char *sm, uns
     }
     sum = wave_sum64(sum);
     if ((threadIdx.x & 63) == 0 && sum && tout) atomicAdd(tout, sum);
-}
-
-// Catalogue of virtual hub v: the last descriptor with v0 <= v.
-__device__ __forceinline__ int graph_of(const GDesc *gd, int ng, uint32_t v) {
-    int lo = 0, hi = ng;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (gd[mid].v0 <= v) lo = mid;
-        else hi = mid;
-    }
-    return lo;
 }
 
 // What the walk over one step table reads or updates.
@@ -1314,7 +1234,12 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
     const double mean_row = nvirt ? (double)sum_e / (double)nvirt : 0.0;
     const bool packed = max_n < (1ull << 24) - 1;
     const Tune3 tune = tuned_for(ctx, tune_key(nb, false, packed, maxdeg, mean_row));
-    const Plan3 P = plan3(ctx, maxdeg, nb, false, false, max_n, mean_row, tune);
+    double cells = 0;   // points per cell, averaged over the points
+    for (int g = 0; g < ng; ++g) cells += gs[g]->cell_points * (double)gs[g]->n;
+    if (nvirt) cells /= (double)nvirt;
+    PlanP PP;
+    const bool paged = planp(ctx, maxdeg, nb, false, false, max_n, mean_row, cells, tune, PP);
+    const Plan3 P = paged ? Plan3() : plan3(ctx, maxdeg, nb, false, false, max_n, mean_row, tune);
     b.ng = ng;
     b.nconf = nconf;
     const size_t per = (size_t)nconf + 1;
@@ -1373,14 +1298,15 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
     a.queue = (uint32_t *)(dv + qoff);
     a.err = (uint32_t *)(dv + (size_t)ng * per);
     a.cfg3 = (const uint16_t *)(dv + coff);
-    set_groups(a, P, nb, false, tune);
+    if (!paged) set_groups(a, P, nb, false, tune);
     if (nvirt > 0 && use_tiles) {
         enqueue_tiles(s, tp, nullptr, a.gd, ng, 0, (uint32_t)nvirt, dv + poff, dv + koff, (uint32_t *)(dv + toff));
         a.tiles = (uint32_t *)(dv + toff);
         a.ntiles = tp.T();
     }
     if (nvirt > 0) {
-        if (P.block == 512) launch3_batch<512>(ctx, s, a, P);
+        if (paged) launchp(ctx, s, a, PP, false, false, true, false, b.rows);
+        else if (P.block == 512) launch3_batch<512>(ctx, s, a, P);
         else if (P.block == 128) launch3_batch<128>(ctx, s, a, P);
         else launch3_batch<256>(ctx, s, a, P);
     }
@@ -1401,8 +1327,17 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     const double mean_row = g.n ? (double)g.n_edges / (double)g.n : 0.0;
     const bool packed = (uint64_t)g.n < (1ull << 24) - 1;
     const Tune3 tune = force ? *force : tuned_for(ctx, tune_key(nb, weighted, packed, maxdeg, mean_row));
-    const Plan3 P = plan3(ctx, maxdeg, nb, weighted, anchored, (uint64_t)g.n, mean_row, tune);
     const int W = g.n_windows;
+    // the paged table where it serves, else the hash table
+    uint64_t max_rows = g.n_edges;   // entries the spoke rows of one launch span
+    if (W > 1) {
+        max_rows = 1;
+        for (int w = 0; w < W; ++w) max_rows = std::max<uint64_t>(max_rows, g.win_edge[w + 1] - g.win_edge[w]);
+    }
+    PlanP PP;
+    const bool paged = max_rows < kWideSpan && planp(ctx, maxdeg, nb, weighted, anchored, (uint64_t)g.n, mean_row,
+                                                     g.cell_points, tune, PP);
+    const Plan3 P = paged ? Plan3() : plan3(ctx, maxdeg, nb, weighted, anchored, (uint64_t)g.n, mean_row, tune);
     const int ntiles = W * (W + 1) / 2;
     int kused = 1;          // hubs per group of the launches (reported in the timings)
 
@@ -1461,7 +1396,7 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     if (!cfg.empty())
         GS_HIP(hipMemcpyAsync(dv + coff, cfg.data(), cfg.size() * 2, hipMemcpyHostToDevice, s));
     GS_HIP(hipEventRecord(ctx.ev[2], s));
-    DevBuf mark;
+    DevBuf mark, rowbuf;
     if (anchored && W == 1 && g.n > 0) {
         mark.alloc((size_t)g.n);
         k_mark_anchor_hubs<<<(unsigned)((g.n + 255) / 256), 256, 0, s>>>(
@@ -1481,19 +1416,26 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
             a.h1 = std::min<uint32_t>(sample_hi, (uint32_t)g.n);
         }
         a.queue = queues;
-        if (use_tiles) {
+        // (few hubs: the three tile kernels cost more than the balance gains,
+        // 1.13 against 1.38 ms for an estimate on 3000 + 3000 points)
+        if (use_tiles && !(paged && a.h1 - a.h0 < 12288)) {
             const TilePlan t1 = tile_plan(ctx, a.h1 - a.h0);
             enqueue_tiles(s, t1, a.rp, nullptr, 0, a.h0, a.h1, hpre, ctot, tbounds);
             a.tiles = tbounds;
             a.ntiles = t1.T();
         }
         const bool wide = wide_rows(g.n_edges);
+        if (paged) {
+            kused = PP.kmax;
+            launchp(ctx, s, a, PP, weighted, anchored, false, wide, rowbuf);
+        } else {
         set_groups(a, P, nb, wide, tune);
         kused = a.kmax;
         // spoke rows of one hub can lie 2^32 entries apart only in graphs
         // that large (GS_WIDE_SPAN forces segments, for tests)
         const bool seg = wide && (g.n_edges >= kWideSpan || getenv("GS_WIDE_SPAN") != nullptr);
         launch3_any(ctx, s, a, P, weighted, anchored, wide, seg);
+        }
     } else if (g.n > 0) {
         // host-tiled graph: spoke window S resident, hub windows H <= S
         // streamed through; copies of the next tile's windows overlap the
@@ -1572,9 +1514,14 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
                 b.ntiles = tt.T();
             }
             const bool wide = wide_rows(maxE);
-            set_groups(b, P, nb, wide, tune);
-            kused = b.kmax;
-            launch3_any(ctx, s, b, P, weighted, anchored, wide);
+            if (paged) {
+                kused = PP.kmax;
+                launchp(ctx, s, b, PP, weighted, anchored, false, wide, rowbuf);
+            } else {
+                set_groups(b, P, nb, wide, tune);
+                kused = b.kmax;
+                launch3_any(ctx, s, b, P, weighted, anchored, wide);
+            }
             if (t.hslot >= 0) GS_HIP(hipEventRecord(ev_hfree[t.hslot], s));
             if (t.last_of_S) GS_HIP(hipEventRecord(ev_sfree[sk], s));
         }
@@ -1604,10 +1551,10 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     ctx.t.kernel_ms = kms;
     ctx.t.kernel_launches = g.n > 0 ? (uint64_t)ntiles : 0;
     ctx.t.probes = h[3 * (size_t)nconf + 2];
-    ctx.t.table_log2 = P.log2h;
-    ctx.t.block = P.block;
+    ctx.t.table_log2 = paged ? 0 : P.log2h;
+    ctx.t.block = paged ? PP.block : P.block;
     ctx.t.group = kused;
-    ctx.t.hash_load = P.hload;
+    ctx.t.hash_load = paged ? 0 : P.hload;
     // merge-walk bytes: each hub-spoke step reads both forward half-lists,
     // 5 bytes per entry: 2.5 B x sum_i m_i^2 over full degrees m_i
     ctx.t.alg_bytes = g.stats_ready ? (uint64_t)(2.5 * (double)g.sum_sq_deg) : 0;
@@ -1644,15 +1591,28 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
     };
 
     // the built-in schedule, spelled out
-    const Plan3 P0 = plan3(ctx, g.max_deg, nb, weighted, false, (uint64_t)g.n, mean_row, Tune3());
     Tune3 cur;
-    cur.block = P0.block;
-    cur.glog = P0.glog;
-    cur.tmax = (int)P0.tmax;
-    cur.mode = P0.mode;
-    cur.hload = P0.hload;
-    cur.trunc = P0.trunc;
-    cur.group = packed && nb <= 64 && !wide ? kMaxGroup : 1;
+    PlanP PP;
+    const bool paged = g.n_edges < kWideSpan &&
+                       planp(ctx, g.max_deg, nb, weighted, false, (uint64_t)g.n, mean_row, g.cell_points, Tune3(), PP);
+    if (paged) {
+        cur.block = PP.block;
+        cur.glog = PP.glog;
+        cur.tmax = 128;   // (fixed)
+        cur.mode = PP.mode;
+        cur.hload = 5;   // (no hash table, no truncation switch)
+        cur.trunc = 1;
+        cur.group = PP.kmax;
+    } else {
+        const Plan3 P0 = plan3(ctx, g.max_deg, nb, weighted, false, (uint64_t)g.n, mean_row, Tune3());
+        cur.block = P0.block;
+        cur.glog = P0.glog;
+        cur.tmax = (int)P0.tmax;
+        cur.mode = P0.mode;
+        cur.hload = P0.hload;
+        cur.trunc = P0.trunc;
+        cur.group = packed && nb <= 64 && !wide ? kMaxGroup : 1;
+    }
 
     // the sample: every hub when a full count takes under ~30 ms, else a
     // centred hub run grown (or shrunk) to 10..40 ms but never below 64 hubs
@@ -1689,7 +1649,7 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
     if (n > 0) {
         // counter addressing
         for (int m : {kLut, kCube, kRank}) {
-            if (m == cur.mode) continue;
+            if (m == cur.mode || (paged && m == kRank)) continue;
             if (m == kLut && nb > kLutMaxBins) continue;
             if (m == kCube && (nb > kCubeMaxBins || weighted)) continue;
             Tune3 t = cur;
@@ -1700,7 +1660,7 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
         const int g0 = cur.glog;
         for (int d : {-1, 1, -2, 2}) {
             const int gl = g0 + d;
-            if (gl < 0 || gl > 6) continue;
+            if (gl < (paged ? 4 : 0) || gl > 6) continue;
             Tune3 t = cur;
             t.glog = gl;
             consider(t);
@@ -1713,19 +1673,20 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
                 consider(t);
             }
         // hash table load
-        {
+        if (!paged) {
             Tune3 t = cur;
             t.hload = cur.hload == 5 ? 7 : 5;
             consider(t);
         }
         // spoke-row truncation
-        {
+        if (!paged) {
             Tune3 t = cur;
             t.trunc = cur.trunc ? 0 : 1;
             consider(t);
         }
         // step table and work-group size
         for (int f : {2, 4}) {
+            if (paged) break;
             Tune3 t = cur;
             t.tmax = f == 2 ? cur.tmax / 2 : cur.tmax * 2;
             if (t.tmax >= 128 && t.tmax <= 8192) consider(t);
