@@ -65,6 +65,9 @@ struct C4Args {
     int lds_cnt;                // counters held in LDS (0: 6-edge counts go to global memory)
     const double *pixdir;       // pixel kind: the 256 pixel centre directions (x, y, z each)
     uint32_t h0, h1;            // hubs of this launch (a host-tiled graph: one window)
+    uint32_t dlo, dhi;          // of those, the ones with dlo <= forward degree <= dhi
+    uint32_t run;               // adjacency-byte kernel: hubs a claim looks through
+    uint32_t parts;             // and parts of a hub (rows part, part + parts, ...)
 };
 
 
@@ -697,7 +700,7 @@ __global__ __launch_bounds__(BLOCK) void k_count4(C4Args a) {
         if (i == kEmptyKey) break;
         const uint64_t beg = a.rp[i];
         const uint32_t d = (uint32_t)(a.rp[i + 1] - beg);
-        if (d < 3) { __syncthreads(); continue; }
+        if (d < a.dlo || d > a.dhi) { __syncthreads(); continue; }
         const double xi = a.X[i], yi = a.Y[i], zi = a.Z[i];
         const uint32_t pi = PERM ? a.perm[i] : 0;
         // every vertex of this hub's cliques lies within rmax of the hub and
@@ -912,6 +915,534 @@ __global__ __launch_bounds__(BLOCK) void k_count4(C4Args a) {
     if (tid == 0 && *s_cnt) atomicAdd(a.ncl, *s_cnt);
 }
 
+// ---- adjacency bytes: hubs of up to a few hundred spokes ----
+//
+// The kernel above finds a clique's third vertex in a bitset and then works
+// everything else out again from coordinates: three separations, their bins,
+// all three vertex records. Here the hub's local graph is a triangle of bytes
+// in LDS, (b, c) -> bin + 1 or 0, filled from the spokes' CSR rows, whose bins
+// are the separations' bins already. A wavefront takes a row a, compacts its
+// neighbours into a list with what belongs to the pair (a, c) -- the bin, the
+// squared length, the pixels -- worked out once for all cliques through that
+// edge, and walks the list's pairs (b, c), 4 x 16 at a time: one byte read
+// decides the pair and gives its bin. The 6-edge count then needs no
+// coordinates at all: a clique's code is a sum of terms of b, of c and of the
+// byte. The parity kinds still compact their cliques in a ring, so that the
+// float64 work runs on full wavefronts, with vertex a in scalar registers.
+// Measured on the 2e5-point clustered counts (1.9e10 4-cliques): vector
+// instructions per 64 cliques fell from 305 to 160 (parity), which the
+// kernel is bound by (vector issue 72% busy, LDS 59%). Parity counts (8 bins)
+// 253 to 119 ms, 438 to 117 where a hub of 424 spokes left the kernel above
+// one work group per CU; 6-edge counts (4 bins) 183 to 38 ms; pixel counts
+// of 1e5 points 326 to 113 ms.
+//
+// LDS is sized by the largest degree of a launch. While every hub fits half a
+// CU's LDS, 512 lanes with two groups per CU are faster (2e5 uniform points,
+// up to 139 spokes: 15.1 ms against 19.0 for 1024 lanes); larger hubs go out
+// in a launch of their own before them, 1024 lanes with the whole LDS, and
+// the bitset kernel takes what that does not hold. A crowded hub of 400
+// spokes is 5 ms of one CU's time and its neighbours are as crowded, so
+// claims of consecutive hubs left most CUs waiting (parity 133 to 168 ms, by
+// the catalogue, against 119 with single claims): a claim's hubs lie evenly
+// over the label range, and a large hub goes out in four parts, every fourth
+// row each (pixel counts 120 ms whole, 115 in halves, 113 in quarters, 114 in
+// eighths: every part builds the hub's bytes).
+
+constexpr int kRing4 = 128;
+
+struct Layout4m {
+    uint32_t pv, pw, wlo, whi, hist, tab, lut, tab6, pdir, pperm, spix, pb, M, stage, hkey, hloc, mstart, mpref,
+        lists, wave, ring, lq, l2, wtot, misc, total;
+};
+
+// Doubles per vertex record (slots of VRec; the pixel kind keeps positions
+// only). Parity: 80 bytes where LDS allows (see VRec), 64 in the wide form,
+// which holds hubs of 443 spokes then instead of 427.
+constexpr int rec4m(int block, int kind) { return kind == kSix4 ? 0 : kind == kPixel4 ? 3 : block > 512 ? 8 : 10; }
+
+// d: largest degree; lq: list entries carry a double (squared length).
+__host__ __device__ inline Layout4m layout4m(int block, uint32_t H, uint32_t d, int ncnt, int nb, bool anchored,
+                                             int kind, bool weighted, int tab6, bool lq) {
+    Layout4m L{};
+    uint32_t o = 0;
+    const bool spokes = kind != kSix4;
+    L.pv = o;      if (spokes) o = lds_align(o + 8 * rec4m(block, kind) * d, 16);
+    L.pw = o;      if (weighted && !spokes) o = lds_align(o + 8 * d, 16);
+    L.wlo = o;     if (weighted) o = lds_align(o + 8 * ncnt, 16);
+    L.whi = o;     if (weighted) o = lds_align(o + 8 * ncnt, 16);
+    L.hist = o;    o = lds_align(o + 4 * ncnt, 16);
+    L.tab = o;     if (spokes) o = lds_align(o + 8 * (nb + 1), 16);
+    L.lut = o;     if (spokes && nb <= kLut4MaxBins) o = lds_align(o + (2u << (3 * lut_shift(nb))), 16);
+    L.tab6 = o;    o = lds_align(o + 2 * tab6, 16);
+    L.pdir = o;    if (kind == kPixel4) o = lds_align(o + 8 * 3 * 256, 16);
+    L.pperm = o;   if (anchored || kind == kPixel4) o = lds_align(o + 4 * d, 16);
+    L.spix = o;    if (kind == kPixel4) o = lds_align(o + 2 * d, 16);
+    L.pb = o;      o = lds_align(o + d, 16);
+    L.M = o + 16;  o = lds_align(o + 32 + d * (d - 1) / 2, 16);
+    L.wtot = o;    o = lds_align(o + 4 * (block / 64 + 1), 16);
+    L.misc = o;    o = lds_align(o + 32, 16);
+    // staging of a hub, then the wavefronts' lists and rings
+    L.stage = o;
+    uint32_t s = o;
+    L.hkey = s;    s = lds_align(s + 4 * H, 16);
+    L.hloc = s;    s = lds_align(s + 2 * H, 16);
+    L.mstart = s;  s = lds_align(s + 8 * block, 16);
+    L.mpref = s;   s = lds_align(s + 4 * (block + 1), 16);
+    uint32_t w = 0;   // per wavefront
+    L.lq = w;      if (lq) w = lds_align(w + 8 * d, 16);
+    L.lists = w;   w = lds_align(w + 4 * d, 16);
+    L.l2 = w;      if (kind == kSix4) w = lds_align(w + 4 * d, 16);
+    if (kind == kPixel4) w = lds_align(w + 2 * d, 16);
+    L.ring = w;    if (spokes) w = lds_align(w + 4 * kRing4, 16);
+    L.wave = w;
+    L.total = std::max(s, o + w * (uint32_t)(block / 64));
+    return L;
+}
+
+// One parity clique {i, a, b, c} of hub i: a's record in registers, b and c
+// by list position (see eval_clique for the decision).
+template <bool LUT, bool WEIGHTED, bool LQ, int ST>
+__device__ __forceinline__ void eval_clique_m(const Stage4 &S, uint32_t hist_addr, uint32_t va, const P3 &A,
+                                              const P3 &ia, double qa, int ba, double wa, const uint32_t *list,
+                                              const double *lq, uint32_t t, double eb, bool wrap, double wi) {
+    const uint32_t pb_ = t & 0xFFFu, pc_ = (t >> 12) & 0xFFFu;
+    const uint32_t eB = list[pb_], eC = list[pc_];
+    const uint32_t vb = eB & 0xFFFu, vc = eC & 0xFFFu;
+    const int bab = (int)((eB >> 12) & 255u), bac = (int)((eC >> 12) & 255u), bbc = (int)(t >> 24) - 1;
+    const int bb = (int)(eB >> 20), bc = (int)(eC >> 20);
+    const double qb = vq<ST>(S, vb), qc = vq<ST>(S, vc);
+    double qab, qac, qbc, Vc;
+    {
+        const P3 B = vpos<ST>(S, vb), C = vpos<ST>(S, vc);
+        const double L = S.L, h = S.half;
+        P3 v{__dsub_rn(C.x, B.x), __dsub_rn(C.y, B.y), __dsub_rn(C.z, B.z)};
+        if (wrap) v = P3{wrap1(v.x, L, h), wrap1(v.y, L, h), wrap1(v.z, L, h)};
+        qbc = sq_len(v.x, v.y, v.z);
+        if (LQ) {
+            qab = lq[pb_];
+            qac = lq[pc_];
+        } else {
+            v = P3{__dsub_rn(B.x, A.x), __dsub_rn(B.y, A.y), __dsub_rn(B.z, A.z)};
+            if (wrap) v = P3{wrap1(v.x, L, h), wrap1(v.y, L, h), wrap1(v.z, L, h)};
+            qab = sq_len(v.x, v.y, v.z);
+            v = P3{__dsub_rn(C.x, A.x), __dsub_rn(C.y, A.y), __dsub_rn(C.z, A.z)};
+            if (wrap) v = P3{wrap1(v.x, L, h), wrap1(v.y, L, h), wrap1(v.z, L, h)};
+            qac = sq_len(v.x, v.y, v.z);
+        }
+        Vc = triple(ia, vspoke<ST>(S, vb), vspoke<ST>(S, vc));
+    }
+    Shared4 sh;
+    sh.Vc = Vc;
+    const double Va = fabs(Vc);
+    const double x = __dsub_rn(Va, eb), y = __dadd_rn(Va, eb);
+    sh.xpos = x > 0.0;
+    sh.x2 = __dmul_rn(x, x);
+    sh.y2 = __dmul_rn(y, y);
+    const uint32_t blk = 4u * (uint32_t)S.nconf;
+    uint32_t o0, o1, o2, o3;   // counter block offsets of the four hubs' channels
+    if (sh.xpos && sh.x2 > S.limR) {
+        o0 = hub_sign(qa, qb, qc, Vc, true, blk);
+        o1 = hub_sign(qa, qab, qac, Vc, false, blk);
+        o2 = hub_sign(qb, qab, qbc, Vc, true, blk);
+        o3 = hub_sign(qc, qac, qbc, Vc, false, blk);
+    } else {
+        int ch[4];
+        bool e0, e1, e2, e3;
+        ch[0] = hub_fast(qa, qb, qc, sh, true, e0);
+        ch[1] = hub_fast(qa, qab, qac, sh, false, e1);
+        ch[2] = hub_fast(qb, qab, qbc, sh, true, e2);
+        ch[3] = hub_fast(qc, qac, qbc, sh, false, e3);
+        const uint32_t mask = (uint32_t)e0 | ((uint32_t)e1 << 1) | ((uint32_t)e2 << 2) | ((uint32_t)e3 << 3);
+        if (mask) exact_hubs<ST>(S, va, vb, vc, wrap, mask, ch);
+        o0 = blk * (uint32_t)ch[0];
+        o1 = blk * (uint32_t)ch[1];
+        o2 = blk * (uint32_t)ch[2];
+        o3 = blk * (uint32_t)ch[3];
+    }
+    const uint32_t a0 = conf_addr<LUT>(S, hist_addr, ba, bb, bc) + o0;
+    const uint32_t a1 = conf_addr<LUT>(S, hist_addr, ba, bab, bac) + o1;
+    const uint32_t a2 = conf_addr<LUT>(S, hist_addr, bb, bab, bbc) + o2;
+    const uint32_t a3 = conf_addr<LUT>(S, hist_addr, bc, bac, bbc) + o3;
+    __hip_atomic_fetch_add((lds_u32 *)(size_t)a0, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add((lds_u32 *)(size_t)a1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add((lds_u32 *)(size_t)a2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add((lds_u32 *)(size_t)a3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (WEIGHTED) {
+        bool ng;
+        const double xw = clique_term(wi, wa, vw<ST>(S, vb), vw<ST>(S, vc), S.wmul, ng);
+        add_term<true>(S, (a0 - hist_addr) >> 2, xw, ng);
+        add_term<true>(S, (a1 - hist_addr) >> 2, xw, ng);
+        add_term<true>(S, (a2 - hist_addr) >> 2, xw, ng);
+        add_term<true>(S, (a3 - hist_addr) >> 2, xw, ng);
+    }
+}
+
+// One pixel-parity clique: the pixels of the spokes and of (a, b), (a, c) are
+// staged; only (b, c)'s is worked out here (see eval_pixel).
+template <bool LUT>
+__device__ __forceinline__ void eval_pixel_m(const Stage4 &S, uint32_t hist_addr, int ba, uint32_t pixa, uint32_t oa,
+                                             const uint32_t *list, const uint16_t *lpx, const uint16_t *spix,
+                                             uint32_t t, bool wrap, uint32_t oi) {
+    constexpr int ST = rec4m(512, kPixel4);
+    const uint32_t pb_ = t & 0xFFFu, pc_ = (t >> 12) & 0xFFFu;
+    const uint32_t eB = list[pb_], eC = list[pc_];
+    const uint32_t vb = eB & 0xFFFu, vc = eC & 0xFFFu;
+    const int bab = (int)((eB >> 12) & 255u), bac = (int)((eC >> 12) & 255u), bbc = (int)(t >> 24) - 1;
+    const int bb = (int)(eB >> 20), bc = (int)(eC >> 20);
+    const P3 B = vpos<ST>(S, vb), C = vpos<ST>(S, vc);
+    P3 v{__dsub_rn(C.x, B.x), __dsub_rn(C.y, B.y), __dsub_rn(C.z, B.z)};
+    if (wrap) v = P3{wrap1(v.x, S.L, S.half), wrap1(v.y, S.L, S.half), wrap1(v.z, S.L, S.half)};
+    uint32_t fbc, rbc;
+    pixel_pair(v, fbc, rbc);
+    const uint32_t pB = spix[vb], pC = spix[vc], pAB = lpx[pb_], pAC = lpx[pc_];   // forward | reverse << 8
+    const uint32_t ob = S.pperm[vb], oc = S.pperm[vc];
+    const int ch0 = hub_pixel(S.pdir, oa, pixa & 255u, ob, pB & 255u, oc, pC & 255u);
+    const int ch1 = hub_pixel(S.pdir, oi, pixa >> 8, ob, pAB & 255u, oc, pAC & 255u);
+    const int ch2 = hub_pixel(S.pdir, oi, pB >> 8, oa, pAB >> 8, oc, fbc);
+    const int ch3 = hub_pixel(S.pdir, oi, pC >> 8, oa, pAC >> 8, ob, rbc);
+    const uint32_t blk = 4u * (uint32_t)S.nconf;
+    const uint32_t a0 = conf_addr<LUT>(S, hist_addr, ba, bb, bc) + blk * (uint32_t)ch0;
+    const uint32_t a1 = conf_addr<LUT>(S, hist_addr, ba, bab, bac) + blk * (uint32_t)ch1;
+    const uint32_t a2 = conf_addr<LUT>(S, hist_addr, bb, bab, bbc) + blk * (uint32_t)ch2;
+    const uint32_t a3 = conf_addr<LUT>(S, hist_addr, bc, bac, bbc) + blk * (uint32_t)ch3;
+    __hip_atomic_fetch_add((lds_u32 *)(size_t)a0, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add((lds_u32 *)(size_t)a1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add((lds_u32 *)(size_t)a2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add((lds_u32 *)(size_t)a3, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// KIND, VAR as k_count4. LQ: lists carry the squared lengths (parity).
+template <int BLOCK, int KIND, bool ANCHORED, int VAR, bool WEIGHTED, bool LQ>
+__global__ __launch_bounds__(BLOCK, 4) void k_count4m(C4Args a) {
+    extern __shared__ __align__(16) unsigned char sm[];
+    const uint32_t H = 1u << a.log2h, mask = H - 1;
+    constexpr bool SIX = KIND == kSix4;
+    constexpr bool LUT = !SIX && VAR == 1;
+    constexpr bool PERM = ANCHORED || KIND == kPixel4;
+    constexpr bool TAB6 = SIX && VAR == 0;
+    constexpr bool CNT_LDS = !SIX || VAR < 2;
+    const int n6c = a.nb * a.nb * a.nb * a.nb * a.nb * a.nb;
+    const Layout4m L = layout4m(BLOCK, H, a.maxdeg, a.lds_cnt, a.nb, ANCHORED, KIND, WEIGHTED, TAB6 ? n6c : 0, LQ);
+    constexpr int ST = rec4m(BLOCK, KIND);
+    double *pv = (double *)__builtin_assume_aligned(sm + L.pv, 16);
+    double *pw = (double *)(sm + L.pw);
+    uint8_t *pb = (uint8_t *)(sm + L.pb), *M = (uint8_t *)(sm + L.M);
+    uint32_t *pperm = (uint32_t *)(sm + L.pperm);
+    uint16_t *spix = (uint16_t *)(sm + L.spix);
+    uint32_t *hkey = (uint32_t *)(sm + L.hkey);
+    uint16_t *hloc = (uint16_t *)(sm + L.hloc);
+    unsigned long long *mstart = (unsigned long long *)(sm + L.mstart);
+    uint32_t *mpref = (uint32_t *)(sm + L.mpref);
+    uint32_t *hist = (uint32_t *)(sm + L.hist);
+    int *ta = (int *)(sm + L.tab), *tb = ta + (a.nb + 1);
+    uint16_t *lut = (uint16_t *)(sm + L.lut), *tab6 = (uint16_t *)(sm + L.tab6);
+    double *pdir = (double *)(sm + L.pdir);
+    uint32_t *wtot = (uint32_t *)(sm + L.wtot);
+    uint32_t *s_hub = (uint32_t *)(sm + L.misc), *s_row = s_hub + 1, *s_part = s_hub + 4;
+    unsigned long long *s_cnt = (unsigned long long *)(sm + L.misc + 8);
+    unsigned long long *wlo = (unsigned long long *)(sm + L.wlo), *whi = (unsigned long long *)(sm + L.whi);
+    const int tid = threadIdx.x, lane = tid & 63;
+    unsigned char *mine = sm + L.stage + (uint32_t)(tid >> 6) * L.wave;
+    uint32_t *list = (uint32_t *)(mine + L.lists);      // c | bin(a, c) << 12 | spoke bin << 20; 6-edge: c | c's term << 12
+    double *lq = (double *)(mine + L.lq);                // squared length of (a, c)
+    uint32_t *lb = (uint32_t *)(mine + L.l2);            // 6-edge: b's term
+    uint16_t *lpx = (uint16_t *)(mine + L.l2);           // pixels of (a, c)
+    uint32_t *ring = (uint32_t *)(mine + L.ring);
+
+    if (KIND == kPixel4)
+        for (int t = tid; t < 3 * 256; t += BLOCK) pdir[t] = a.pixdir[t];
+    for (int b = tid; b < a.lds_cnt; b += BLOCK) {
+        hist[b] = 0;
+        if (WEIGHTED) {
+            wlo[b] = 0;
+            whi[b] = 0;
+        }
+    }
+    if (TAB6)
+        for (int t = tid; t < n6c; t += BLOCK) tab6[t] = (uint16_t)a.cfg6[t];
+    const int lsh = lut_shift(a.nb);
+    if (!SIX) {
+        for (int b = tid; b < a.nb; b += BLOCK) {
+            ta[b] = rank_a(a.nb, b);
+            tb[b] = rank_b(a.nb, b);
+        }
+        if (LUT)
+            for (int t = tid; t < (1 << (3 * lsh)); t += BLOCK) {
+                const int m = (1 << lsh) - 1;
+                const int x = t >> (2 * lsh), y = (t >> lsh) & m, z = t & m;
+                const int b0 = min(min(x, y), z), b2 = max(max(x, y), z), b1 = x + y + z - b0 - b2;
+                lut[t] = (x < a.nb && y < a.nb && z < a.nb) ? (uint16_t)(4 * (rank_a(a.nb, b0) + rank_b(a.nb, b1) + b2))
+                                                           : (uint16_t)0;
+            }
+    }
+    if (tid == 0) *s_cnt = 0;
+    __syncthreads();
+
+    unsigned long long mycl = 0;   // cliques of this wavefront (lane 0)
+    uint64_t acc = 0;
+    HubCursor cursor;
+    uint64_t pend = 0;             // first wavefront: claimed hubs base + bit still to do
+    uint32_t base = 0;
+    // unit u of a launch is part u / perpart of a hub; the hubs of a claim
+    // of several (a.run) lie evenly over the range
+    const uint32_t step = max(1u, (a.h1 - a.h0 + a.run - 1) / a.run), perpart = step * a.run;
+    auto hub_of = [&](uint32_t u) {
+        const uint32_t r = u % perpart;
+        return a.h0 + r % a.run * step + r / a.run;
+    };
+    const double Lb = a.L, half = a.half;
+    const double tn = a.thr[a.nb];
+    const double limR = __dmul_rn(1e-18, __dmul_rn(__dmul_rn(tn, tn), tn));
+    const Stage4 S{pv, pb, nullptr, ta, tb, lut, hist, a.nb, a.nconf, a.L, a.half,
+                   0.0f, 0.0f, 0.0f, {0.0, 0.0, 0.0}, 0, lsh, limR,
+                   a.wmul, wlo, whi, a.hist, a.wsum, a.cfg6, tab6, pdir, pperm};
+    const uint32_t hist_addr = lds_addr(hist);
+    const uint32_t nb = (uint32_t)a.nb, nb2 = nb * nb, nb3 = nb2 * nb, nb4 = nb3 * nb, nb5 = nb4 * nb;
+
+    while (true) {
+        // the next hub (or part) of this launch's degrees: a claim is looked
+        // through by one wavefront at once
+        if (tid < 64) {
+            while (!pend) {
+                uint32_t v = 0, e = 0;
+                if (lane == 0) {
+                    v = next_hub_in(a.queue, 0, a.parts * perpart, gridDim.x, cursor, a.run);
+                    e = cursor.cur = cursor.end;
+                }
+                v = __builtin_amdgcn_readfirstlane(v);
+                e = __builtin_amdgcn_readfirstlane(e);
+                if (v == kEmptyKey) break;
+                base = v;
+                const uint32_t hub = hub_of(min(v + lane, e - 1));
+                const uint64_t deg = v + lane < e && hub < a.h1 ? a.rp[hub + 1] - a.rp[hub] : 0;
+                pend = __ballot(deg >= a.dlo && deg <= a.dhi);
+            }
+            if (lane == 0) {
+                const uint32_t u = base + (pend ? (uint32_t)__builtin_ctzll(pend) : 0u);
+                *s_hub = pend ? hub_of(u) : kEmptyKey;
+                *s_part = u / perpart;
+            }
+            pend &= pend - 1;
+        }
+        __syncthreads();
+        const uint32_t i = *s_hub;
+        if (i == kEmptyKey) break;
+        const uint64_t beg = a.rp[i];
+        const uint32_t d = (uint32_t)(a.rp[i + 1] - beg);
+        const double xi = a.X[i], yi = a.Y[i], zi = a.Z[i];
+        const uint32_t pi = PERM ? a.perm[i] : 0;
+        const double wi = WEIGHTED ? a.w[i] : 0.0;
+        const bool inner = __builtin_amdgcn_readfirstlane((int)(xi >= a.in_lo && xi <= a.in_hi && yi >= a.in_lo &&
+                                                                 yi <= a.in_hi && zi >= a.in_lo && zi <= a.in_hi)) != 0;
+        // a hub adds at most 4 C(d, 3) increments
+        const uint64_t most = 4ull * d * (d - 1) * (d - 2) / 6;
+        if (acc > 0 && acc + most >= a.flush_limit) {
+            flush4<BLOCK, WEIGHTED>(a, S, hist);
+            acc = 0;
+        }
+        acc += most;
+        // 1. an empty hash and matrix, then the hub's forward row
+        for (uint32_t t = tid; t < H; t += BLOCK) hkey[t] = kEmptyKey;
+        for (uint32_t t = tid; t < (d * (d - 1) / 2 + 15) / 16; t += BLOCK) ((uint4 *)M)[t] = make_uint4(0, 0, 0, 0);
+        if (tid == 0) *s_row = *s_part;
+        __syncthreads();
+        for (uint32_t e = tid; e < d; e += BLOCK) {
+            const uint32_t k = a.col[beg + e];
+            uint32_t s = label_hash(k, a.log2h);
+            while (atomicCAS(&hkey[s], kEmptyKey, k) != kEmptyKey) s = (s + 1) & mask;
+            hloc[s] = (uint16_t)e;
+            if (!SIX) {
+                const double x = a.X[k], y = a.Y[k], z = a.Z[k];
+                double *rec = pv + ST * e;
+                rec[kVx] = x;
+                rec[kVx + 1] = y;
+                rec[kVx + 2] = z;
+                const double dx = min_image(xi, x, Lb, half), dy = min_image(yi, y, Lb, half),
+                             dz = min_image(zi, z, Lb, half);
+                if (KIND == kParity4) {
+                    rec[kVs] = dx;
+                    rec[kVs + 1] = dy;
+                    rec[kVs + 2] = dz;
+                    rec[kVq] = sq_len(dx, dy, dz);
+                    if (WEIGHTED) rec[VRec<KIND, WEIGHTED>::W] = a.w[k];
+                }
+                if (KIND == kPixel4) {
+                    uint32_t f, r;
+                    pixel_pair(P3{dx, dy, dz}, f, r);
+                    spix[e] = (uint16_t)(f | r << 8);
+                }
+            } else if (WEIGHTED) {
+                pw[e] = a.w[k];
+            }
+            pb[e] = a.bin[beg + e];
+            if (PERM) pperm[e] = a.perm[k];
+        }
+        __syncthreads();
+        // 2. the bytes: (spoke s, c) = bin + 1 for every c of s's row that is
+        //    a spoke too
+        for (uint32_t c0 = 0; c0 + 1 < d; c0 += BLOCK) {
+            const uint32_t sidx = c0 + tid;
+            uint32_t len = 0;
+            uint64_t st = 0;
+            if (sidx + 1 < d) {
+                const uint32_t j = a.col[beg + sidx];
+                st = a.rp[j];
+                len = (uint32_t)(a.rp[j + 1] - st);
+            }
+            uint32_t total;
+            const uint32_t pre = wg_excl_scan<BLOCK>(len, wtot, total);
+            mstart[tid] = st;
+            mpref[tid] = pre;
+            if (tid == 0) mpref[BLOCK] = total;
+            __syncthreads();
+            uint32_t sp = 0;
+            for (uint32_t e0 = 0; e0 < total; e0 += BLOCK) {
+                const uint32_t e = e0 + tid;
+                if (e < total) {
+                    while (mpref[sp + 1] <= e) ++sp;
+                    const uint64_t at = mstart[sp] + (e - mpref[sp]);
+                    const uint32_t k = a.col[at];
+                    const uint8_t bn = a.bin[at];
+                    uint32_t h = label_hash(k, a.log2h), key;
+                    while ((key = hkey[h]) != k && key != kEmptyKey) h = (h + 1) & mask;
+                    if (key == k) {
+                        const uint32_t r = c0 + sp, c = hloc[h];   // c > r: rows ascend
+                        M[r * (2 * d - r - 1) / 2 + (c - r - 1)] = (uint8_t)(bn + 1u);
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        // 3. rows, claimed by the wavefronts (the longest come first)
+        while (true) {
+            uint32_t ra = 0;
+            if (lane == 0) ra = atomicAdd(s_row, a.parts);
+            ra = __builtin_amdgcn_readfirstlane(ra);
+            if (ra + 2 >= d) break;
+            const uint8_t *Ma = M + ra * (2 * d - ra - 1) / 2;   // (a, a + 1 + n) at n
+            const uint32_t na = d - 1 - ra;
+            const int ba = pb[ra];
+            P3 A{0, 0, 0}, ia{0, 0, 0};
+            double qa = 0, wa = 0;
+            if (!SIX) {
+                A = vpos<ST>(S, ra);
+                if (KIND == kParity4) {
+                    ia = vspoke<ST>(S, ra);
+                    qa = vq<ST>(S, ra);
+                    if (WEIGHTED) wa = vw<ST>(S, ra);
+                }
+            } else if (WEIGHTED) {
+                wa = pw[ra];
+            }
+            const uint32_t pa = PERM ? pperm[ra] : 0u, pm = ANCHORED ? min(pi, pa) : 0u;
+            const uint32_t pixa = KIND == kPixel4 ? spix[ra] : 0u;
+            // 3a. the row's neighbours with what belongs to the edge (a, c)
+            uint32_t m = 0;
+            for (uint32_t n0 = 0; n0 < na; n0 += 64) {
+                const uint32_t n = n0 + lane;
+                const uint32_t v = n < na ? (uint32_t)Ma[n] : 0u;
+                const uint64_t bal = __ballot(v != 0);
+                if (v) {
+                    const uint32_t at = m + lanes_below(bal), c = ra + 1 + n, bac = v - 1, bc = pb[c];
+                    if (SIX) {
+                        list[at] = c | (bc * nb3 + bac * nb) << 12;
+                        lb[at] = bc * nb4 + bac * nb2;
+                    } else {
+                        list[at] = c | bac << 12 | bc << 20;
+                        if (LQ || KIND == kPixel4) {
+                            const P3 C = vpos<ST>(S, c);
+                            P3 u{__dsub_rn(C.x, A.x), __dsub_rn(C.y, A.y), __dsub_rn(C.z, A.z)};
+                            if (!inner) u = P3{wrap1(u.x, Lb, half), wrap1(u.y, Lb, half), wrap1(u.z, Lb, half)};
+                            if (LQ) lq[at] = sq_len(u.x, u.y, u.z);
+                            if (KIND == kPixel4) {
+                                uint32_t f, r;
+                                pixel_pair(u, f, r);
+                                lpx[at] = (uint16_t)(f | r << 8);
+                            }
+                        }
+                    }
+                }
+                m += (uint32_t)__popcll(bal);
+            }
+            if (m < 2) continue;
+            wave_lds_sync();
+            // 3b. the list's pairs: 4 entries b by 16 entries c at a time
+            uint32_t qhead = 0, qtail = 0;   // ring positions (wavefront-uniform)
+            auto evaluate = [&](uint32_t t) {
+                if (KIND == kPixel4) {
+                    eval_pixel_m<LUT>(S, hist_addr, ba, pixa, pa, list, lpx, spix, t, !inner, pi);
+                } else if (KIND == kParity4) {
+                    eval_clique_m<LUT, WEIGHTED, LQ, ST>(S, hist_addr, ra, A, ia, qa, ba, wa, list, lq, t,
+                                                     inner ? a.eb_in : a.eb_wrap, !inner, wi);
+                }
+            };
+            const uint32_t code0 = (uint32_t)ba * nb5 - 1u;
+            for (uint32_t p = 0; p + 1 < m; p += 4) {
+                const uint32_t bp = p + ((uint32_t)lane >> 4);
+                const uint32_t b = list[min(bp, m - 1)] & 0xFFFu;
+                // (b, c) at rowb + c (in bounds, if meaningless, also for c <= b)
+                const uint8_t *rowb = M + (int)(b * (2 * d - b - 1) / 2) - (int)(b + 1);
+                const uint32_t cb = SIX ? code0 + lb[min(bp, m - 1)] : 0u;
+                const uint32_t pmb = ANCHORED ? min(pm, pperm[b]) : 0u;
+                const double wb = SIX && WEIGHTED ? pw[b] : 0.0;
+                for (uint32_t q = p + 1; q < m; q += 16) {
+                    const uint32_t cp = q + ((uint32_t)lane & 15u);
+                    const uint32_t ec = list[min(cp, m - 1)];
+                    const uint32_t c = ec & 0xFFFu;
+                    const uint32_t v = rowb[c];
+                    bool take = v != 0 && cp < m && cp > bp;
+                    if (ANCHORED) {
+                        const uint32_t mn = min(pmb, pperm[c]);
+                        take = take && mn >= a.anchor_lo && mn < a.anchor_hi;
+                    }
+                    const uint64_t bal = __ballot(take);
+                    if (SIX) {
+                        if (lane == 0) mycl += (unsigned long long)__popcll(bal);
+                        const uint32_t code = cb + (ec >> 12) + v;
+                        if (take) {
+                            const uint32_t cfg = TAB6 ? (uint32_t)tab6[code] : a.cfg6[code];
+                            if (CNT_LDS)
+                                __hip_atomic_fetch_add((lds_u32 *)(size_t)(hist_addr + 4 * cfg), 1u, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                            else
+                                atomicAdd(&a.hist[cfg], 1ull);
+                            if (WEIGHTED) {
+                                bool ng;
+                                const double x = clique_term(wi, wa, wb, pw[c], S.wmul, ng);
+                                add_term<CNT_LDS>(S, cfg, x, ng);
+                            }
+                        }
+                    } else if (bal) {
+                        if (take)
+                            ring[(qtail + lanes_below(bal)) & (kRing4 - 1)] = bp | cp << 12 | v << 24;
+                        qtail += (uint32_t)__popcll(bal);
+                        if (qtail - qhead >= 64) {
+                            wave_lds_sync();
+                            const uint32_t t = ring[(qhead + lane) & (kRing4 - 1)];
+                            qhead += 64;
+                            evaluate(t);
+                            wave_lds_sync();
+                        }
+                    }
+                }
+            }
+            if (!SIX) {
+                wave_lds_sync();
+                if ((uint32_t)lane < qtail - qhead) evaluate(ring[(qhead + lane) & (kRing4 - 1)]);
+                if (lane == 0) mycl += qtail;
+            }
+            wave_lds_sync();   // the list is free for the next row
+        }
+        __syncthreads();
+    }
+
+    __syncthreads();
+    flush4<BLOCK, WEIGHTED>(a, S, hist);
+    if (mycl) atomicAdd(s_cnt, mycl);
+    __syncthreads();
+    if (tid == 0 && *s_cnt) atomicAdd(a.ncl, *s_cnt);
+}
+
 __global__ void k_zero4(unsigned long long *p, uint64_t n) {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (uint64_t)gridDim.x * blockDim.x)
@@ -945,6 +1476,36 @@ template <int BLOCK, int KIND, int VAR>
 void launch4_v(Ctx &ctx, const C4Args &a, uint32_t lds, bool anchored, bool wt) {
     if (anchored) wt ? launch4<BLOCK, KIND, true, VAR, true>(ctx, a, lds) : launch4<BLOCK, KIND, true, VAR, false>(ctx, a, lds);
     else wt ? launch4<BLOCK, KIND, false, VAR, true>(ctx, a, lds) : launch4<BLOCK, KIND, false, VAR, false>(ctx, a, lds);
+}
+
+template <int BLOCK, int KIND, bool A, int VAR, bool WT, bool LQ>
+void launch4m(Ctx &ctx, const C4Args &a, uint32_t lds) {
+    const void *kern = reinterpret_cast<const void *>(&k_count4m<BLOCK, KIND, A, VAR, WT, LQ>);
+    if (lds > 65536)
+        GS_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    int per_cu = 0;
+    GS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_count4m<BLOCK, KIND, A, VAR, WT, LQ>, BLOCK, lds));
+    if (per_cu < 1) fail(GS_EUNSUPPORTED, "4-clique kernel does not fit a compute unit");
+    if (getenv("GS_PLAN_LOG"))
+        fprintf(stderr, "[gsn] count4m kind %d var %d block %d lds %u blocks/CU %d degrees %u..%u\n", KIND, VAR, BLOCK,
+                lds, per_cu, a.dlo, a.dhi);
+    uint32_t grid = (uint32_t)ctx.n_cu * (uint32_t)per_cu;
+    grid = (grid + kNumQueues - 1) / kNumQueues * kNumQueues;
+    k_count4m<BLOCK, KIND, A, VAR, WT, LQ><<<dim3(grid), dim3(BLOCK), lds, ctx.stream>>>(a);
+    GS_HIP(hipGetLastError());
+}
+
+// wide: 1024 lanes (no squared lengths in the parity lists).
+template <int KIND, int VAR, bool WT>
+void launch4m_k(Ctx &ctx, const C4Args &a, uint32_t lds, bool anchored, bool wide) {
+    constexpr bool LQ = KIND == kParity4;
+    if (wide) {
+        if (anchored) launch4m<1024, KIND, true, VAR, WT, false>(ctx, a, lds);
+        else launch4m<1024, KIND, false, VAR, WT, false>(ctx, a, lds);
+    } else {
+        if (anchored) launch4m<512, KIND, true, VAR, WT, LQ>(ctx, a, lds);
+        else launch4m<512, KIND, false, VAR, WT, LQ>(ctx, a, lds);
+    }
 }
 
 // The 24 relabellings of a clique's four vertices as permutations of its six
@@ -1113,6 +1674,29 @@ void count4_run(Ctx &ctx, const Graph &g, const Count4Out &o, const gs_anchor_ra
     int BLOCK = 512;
     if (const char *eb = getenv("GS_BLOCK4")) BLOCK = atoi(eb) == 256 ? 256 : 512;
     if (o.kind != kParity4) BLOCK = 512;   // the other kinds are built for 512 lanes only
+    // hubs by degree: [3, d1] and (d1, d2] go to the adjacency-byte kernel
+    // (512 lanes in half a CU's LDS, 1024 lanes in all of it), larger ones to
+    // the bitset kernel (GS_MATRIX4=0: all of them, GS_MATRIX4=2: none to the
+    // 512-lane form, for tests)
+    auto log2_of = [](uint32_t deg) {
+        int l = 6;
+        while ((1u << l) < 2 * deg) ++l;
+        return l;
+    };
+    auto fits = [&](int block, bool lq, uint32_t room) {
+        uint32_t lo = 2, hi = std::min(maxdeg, 1024u);   // largest degree whose layout fits
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1) / 2;
+            if (layout4m(block, 1u << log2_of(mid), mid, lds_cnt, nb, anchored, o.kind, weighted, tab6, lq).total <= room) lo = mid;
+            else hi = mid - 1;
+        }
+        return lo;
+    };
+    const char *em = getenv("GS_MATRIX4");
+    const int matrix = em ? atoi(em) : 1;
+    const uint32_t half_lds = (uint32_t)ctx.max_lds / 2 / 1280 * 1280;
+    const uint32_t d1 = matrix == 1 ? fits(512, o.kind == kParity4, half_lds) : 2;
+    const uint32_t d2 = matrix ? std::max(d1, fits(1024, false, (uint32_t)ctx.max_lds)) : 2;
     Layout4 L = layout4(BLOCK, H, maxdeg, W, lds_cnt, nb, anchored, o.kind, weighted, tab6);
     if ((int)L.total > ctx.max_lds)
         fail(GS_EUNSUPPORTED, "4-clique kernel LDS footprint too large (forward degree " +
@@ -1214,8 +1798,11 @@ void count4_run(Ctx &ctx, const Graph &g, const Count4Out &o, const gs_anchor_ra
     GS_HIP(hipEventRecord(ctx.ev[2], s));
     a.h0 = 0;
     a.h1 = (uint32_t)g.n;
-    auto launch = [&]() {
+    uint64_t launches = 0;
+    auto launch_bits = [&]() {
         const uint32_t lds = L.total;
+        a.maxdeg = maxdeg;
+        a.log2h = log2h;
         if (pixel) {
             if (var == 1) launch4_pixel<1>(ctx, a, lds, anchored);
             else launch4_pixel<0>(ctx, a, lds, anchored);
@@ -1231,10 +1818,47 @@ void count4_run(Ctx &ctx, const Graph &g, const Count4Out &o, const gs_anchor_ra
             else launch4_v<256, kParity4, 0>(ctx, a, lds, anchored, weighted);
         }
     };
-    uint64_t launches = 0;
+    auto launch_bytes = [&](uint32_t top, bool wide) {
+        a.maxdeg = top;
+        a.log2h = log2_of(top);
+        const uint32_t lds = layout4m(wide ? 1024 : 512, 1u << a.log2h, top, lds_cnt, nb, anchored, o.kind, weighted,
+                                      tab6, !wide && o.kind == kParity4).total;
+        if (pixel) {
+            if (var == 1) launch4m_k<kPixel4, 1, false>(ctx, a, lds, anchored, wide);
+            else launch4m_k<kPixel4, 0, false>(ctx, a, lds, anchored, wide);
+        } else if (six) {
+            if (var == 0) weighted ? launch4m_k<kSix4, 0, true>(ctx, a, lds, anchored, wide) : launch4m_k<kSix4, 0, false>(ctx, a, lds, anchored, wide);
+            else if (var == 1) weighted ? launch4m_k<kSix4, 1, true>(ctx, a, lds, anchored, wide) : launch4m_k<kSix4, 1, false>(ctx, a, lds, anchored, wide);
+            else weighted ? launch4m_k<kSix4, 2, true>(ctx, a, lds, anchored, wide) : launch4m_k<kSix4, 2, false>(ctx, a, lds, anchored, wide);
+        } else {
+            if (var == 1) weighted ? launch4m_k<kParity4, 1, true>(ctx, a, lds, anchored, wide) : launch4m_k<kParity4, 1, false>(ctx, a, lds, anchored, wide);
+            else weighted ? launch4m_k<kParity4, 0, true>(ctx, a, lds, anchored, wide) : launch4m_k<kParity4, 0, false>(ctx, a, lds, anchored, wide);
+        }
+    };
+    // the largest hubs first; every launch starts on cleared queues
+    auto launch = [&]() {
+        bool first = true;
+        auto part = [&](uint32_t lo, uint32_t hi, auto &&go) {
+            if (hi < lo || maxdeg < lo) return;
+            if (!first) k_zero4<<<1, 256, 0, s>>>((unsigned long long *)a.queue, kQueueWords / 2);
+            first = false;
+            a.dlo = lo;
+            a.dhi = hi;
+            // few of the hubs are large (their tail shows): those go in four
+            // parts, and a claim looks through 16. Where most are, there is
+            // no tail to shorten (n >= 2^28: 32-bit unit numbers).
+            const bool few = lo > 3 && (double)g.n_edges < 0.5 * (double)d1 * (double)g.n && g.n < (1ull << 28);
+            a.run = few ? 16u : 1u;
+            a.parts = few && hi <= d2 ? 4u : 1u;
+            go();
+            ++launches;
+        };
+        part(std::max(3u, d2 + 1), maxdeg, launch_bits);
+        part(std::max(3u, d1 + 1), std::min(d2, maxdeg), [&] { launch_bytes(std::min(d2, maxdeg), true); });
+        part(3u, std::min(d1, maxdeg), [&] { launch_bytes(std::min(d1, maxdeg), false); });
+    };
     if (g.n > 0 && g.n_windows == 1) {
         launch();
-        launches = 1;
     } else if (g.n > 0) {
         // Host-tiled graph: for each hub window, the CSR entries from its
         // first row through the row of its hubs' largest spoke (every row a
@@ -1273,7 +1897,6 @@ void count4_run(Ctx &ctx, const Graph &g, const Count4Out &o, const gs_anchor_ra
             a.h1 = (uint32_t)g.win[w + 1];
             k_zero4<<<1, 256, 0, s>>>((unsigned long long *)a.queue, kQueueWords / 2);
             launch();
-            ++launches;
         }
         GS_HIP(hipStreamSynchronize(s));
     }
