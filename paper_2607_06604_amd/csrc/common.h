@@ -295,7 +295,10 @@ __host__ __device__ inline int rank_b(int nb, int b2) { return (int)(-c2(nb - b2
 // built-in one.
 void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64_t *ntri,
                 const gs_anchor_range *anchors, const Tune3 *force = nullptr, uint32_t sample_lo = 0,
-                uint32_t sample_hi = 0);
+                uint32_t sample_hi = 0, int nmu = 0);
+// Whether count3_run would take the paged table for such a count (nmu: mu
+// bins; those counts have no other path there).
+bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nmu);
 // Time schedules on a sample of g's hubs and keep the fastest for g's shape.
 void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out);
 // 4-clique counts. kind kParity4 (or kPixel4, parity from direction pixels):

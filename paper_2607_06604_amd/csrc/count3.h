@@ -62,6 +62,11 @@ struct C3Args {
     uint32_t *err;          // bit 1: LDS addressing
     uint64_t wspan;         // WIDE: entries a segment of spoke rows may span from its first row
     const uint16_t *cfg3;   // kLut / kCube: configuration index of ordered triple (x*nb + y)*nb + z
+    int nmu;                // mu counts (else 0): counters per configuration
+    const int4 *q4;         // their positions in units of the box / 2^32 (wrapping)
+    float qscale;           // such a unit over rmax
+    const double *X, *Y, *Z;
+    double L, half;
     const uint32_t *tiles;  // hub tiles of about equal cost: tile t = [tiles[t], tiles[t+1]) (or null)
     uint32_t ntiles;
 };
@@ -88,8 +93,9 @@ struct PlanP {
 
 // The schedule for a graph of the given degrees, or false where the paged
 // table does not serve (then the hash table does).
+// nmu: mu bins (else 0).
 bool planp(const Ctx &ctx, uint32_t maxdeg, int nb, bool weighted, bool anchored, uint64_t n, double mean_row,
-           double cell_points, const Tune3 &tune, PlanP &p);
+           double cell_points, const Tune3 &tune, PlanP &p, int nmu = 0);
 // rows: device memory the launch may need (taken on first use; held by the
 // caller until the launch has completed).
 void launchp(Ctx &ctx, hipStream_t s, const C3Args &a, const PlanP &P, bool weighted, bool anchored, bool batch,
@@ -104,6 +110,39 @@ __device__ __forceinline__ int graph_of(const GDesc *gd, int ng, uint32_t v) {
         else hi = mid;
     }
     return lo;
+}
+
+// mu bin of the triangle with (minimum-image) edge vectors u = p0->p1 and
+// v = p0->p2.
+__device__ __forceinline__ int mu_bin(double ux, double uy, double uz, double vx, double vy, double vz, int nmu) {
+    const double nx = __dsub_rn(__dmul_rn(uy, vz), __dmul_rn(uz, vy));
+    const double ny = __dsub_rn(__dmul_rn(uz, vx), __dmul_rn(ux, vz));
+    const double nz = __dsub_rn(__dmul_rn(ux, vy), __dmul_rn(uy, vx));
+    const double s = __dadd_rn(__dadd_rn(__dmul_rn(nx, nx), __dmul_rn(ny, ny)), __dmul_rn(nz, nz));
+    const double t = __dmul_rn(__dmul_rn(nz, nz), (double)(nmu * nmu));
+    int m = 0;
+    if (s > 0.0)
+        for (int k = 1; k < nmu; ++k) m += t >= __dmul_rn((double)(k * k), s);
+    return m;
+}
+
+// A vertex: absolute coordinates and original index.
+struct P3x {
+    double x, y, z;
+    uint32_t o;
+};
+
+__device__ __forceinline__ void swapx(P3x &a, P3x &b) {
+    const P3x t = a;
+    a = b;
+    b = t;
+}
+
+// Sort three vertices by original index.
+__device__ __forceinline__ void order3(P3x &a, P3x &b, P3x &c) {
+    if (a.o > b.o) swapx(a, b);
+    if (b.o > c.o) swapx(b, c);
+    if (a.o > b.o) swapx(a, b);
 }
 
 __device__ __forceinline__ unsigned long long wave_sum64(unsigned long long v) {

@@ -1177,6 +1177,15 @@ __global__ void k_mark_anchor_hubs(const uint64_t *__restrict__ rp, const uint32
     mark[i] = m;
 }
 
+// Positions in units of the box / 2^32: differences of 32-bit numbers wrap as
+// the box does.
+__global__ void k_box_units(const double *__restrict__ C, uint32_t n, double scale, int4 *__restrict__ q) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    auto unit = [&](double x) { return (int)(uint32_t)(unsigned long long)__double2ll_rn(__dmul_rn(x, scale)); };
+    q[i] = make_int4(unit(C[i]), unit(C[(size_t)n + i]), unit(C[2 * (size_t)n + i]), 0);
+}
+
 uint64_t flush_limit_for(uint32_t maxdeg, uint64_t per_chunk_factor) {
     // GS_FLUSH_LIMIT lowers the flush threshold (exercises the flush path)
     const char *fl = getenv("GS_FLUSH_LIMIT");
@@ -1316,10 +1325,25 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
     GS_HIP(hipEventRecord(b.done, s));
 }
 
+bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nmu) {
+    if (g.n == 0 || g.n_windows != 1 || g.n_edges >= kWideSpan) return false;
+    const double mean_row = (double)g.n_edges / (double)g.n;
+    if (nmu) {
+        // the float32 mu bins take positions in 2^-32 of the box: no wrap
+        // among a triangle's vertices, and rounding well below theirs
+        if (weighted || anchored || wide_rows(g.n_edges)) return false;
+        if (!(4.0 * g.rmax * (1.0 + 1e-9) < g.box && g.box <= 256.0 * g.rmax)) return false;
+    }
+    const bool packed = (uint64_t)g.n < (1ull << 24) - 1;
+    const Tune3 tune = tuned_for(ctx, tune_key(g.nbins, weighted, packed, g.max_deg, mean_row));
+    PlanP p;
+    return planp(ctx, g.max_deg, g.nbins, weighted, anchored, (uint64_t)g.n, mean_row, g.cell_points, tune, p, nmu);
+}
+
 void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64_t *ntri,
-                const gs_anchor_range *anchors, const Tune3 *force, uint32_t sample_lo, uint32_t sample_hi) {
+                const gs_anchor_range *anchors, const Tune3 *force, uint32_t sample_lo, uint32_t sample_hi, int nmu) {
     const int nb = g.nbins;
-    const int nconf = (int)n_configs(nb);
+    const int nconf = (int)n_configs(nb) * std::max(1, nmu);
     const bool weighted = wsum != nullptr;
     const bool anchored = anchors != nullptr;
     if (anchored && (anchors->lo > anchors->hi)) fail(GS_EINVAL, "anchor range lo > hi");
@@ -1336,7 +1360,8 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     }
     PlanP PP;
     const bool paged = max_rows < kWideSpan && planp(ctx, maxdeg, nb, weighted, anchored, (uint64_t)g.n, mean_row,
-                                                     g.cell_points, tune, PP);
+                                                     g.cell_points, tune, PP, nmu);
+    if (nmu && !paged) fail(GS_EUNSUPPORTED, "mu bins need the paged table here");
     const Plan3 P = paged ? Plan3() : plan3(ctx, maxdeg, nb, weighted, anchored, (uint64_t)g.n, mean_row, tune);
     const int ntiles = W * (W + 1) / 2;
     int kused = 1;          // hubs per group of the launches (reported in the timings)
@@ -1396,7 +1421,21 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     if (!cfg.empty())
         GS_HIP(hipMemcpyAsync(dv + coff, cfg.data(), cfg.size() * 2, hipMemcpyHostToDevice, s));
     GS_HIP(hipEventRecord(ctx.ev[2], s));
-    DevBuf mark, rowbuf;
+    DevBuf mark, rowbuf, qbuf;
+    if (nmu && g.n > 0) {
+        qbuf.alloc(16 * (size_t)g.n, ctx.pool);
+        const double *C = g.coords.as<double>();
+        k_box_units<<<(unsigned)((g.n + 255) / 256), 256, 0, s>>>(C, (uint32_t)g.n, 4294967296.0 / g.box, qbuf.as<int4>());
+        GS_HIP(hipGetLastError());
+        a.nmu = nmu;
+        a.q4 = qbuf.as<int4>();
+        a.qscale = (float)(g.box / 4294967296.0 / g.rmax);
+        a.X = C;
+        a.Y = C + g.n;
+        a.Z = C + 2 * g.n;
+        a.L = g.periodic ? g.box : HUGE_VAL;
+        a.half = g.periodic ? 0.5 * g.box : HUGE_VAL;
+    }
     if (anchored && W == 1 && g.n > 0) {
         mark.alloc((size_t)g.n);
         k_mark_anchor_hubs<<<(unsigned)((g.n + 255) / 256), 256, 0, s>>>(

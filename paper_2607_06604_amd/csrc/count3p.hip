@@ -67,14 +67,17 @@ typedef __attribute__((address_space(1))) const double gbl_f64;
 typedef __attribute__((address_space(3))) const uint8_t lds_u8;
 typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 
+constexpr int kMuLane = 2;         // triangles a lane takes at a time
+constexpr uint32_t kMuBuf = 64 * kMuLane + 256;   // triangles of a wavefront: those left over and 4 x 64 new ones
+
 // LDS layout of one work group (byte offsets): the page maps, then the pages
 // (at kPages), so that a map and a page are aligned to their sizes.
 struct LayoutP {
-    uint32_t cnt, lut, step, mw, mperm, misc, total;
+    uint32_t cnt, lut, step, mw, mperm, mj, buf, misc, total;
 };
 
 __host__ __device__ inline LayoutP layoutp(int block, uint32_t tbytes, int nconf, int nb, bool weighted,
-                                           bool anchored, int mode, bool rows) {
+                                           bool anchored, int mode, bool rows, bool mu = false) {
     LayoutP L{};
     uint32_t o = lds_align(kPages + tbytes, 16);
     L.cnt = o;    o = lds_align(o + (mode == kCube ? 4 * nb * nb * nb : (weighted ? 16 : 4) * nconf), 16);
@@ -83,6 +86,8 @@ __host__ __device__ inline LayoutP layoutp(int block, uint32_t tbytes, int nconf
     L.step = o;   o = lds_align(o + std::max(rows ? 0u : 8 * kWaveSteps * (uint32_t)(block / 64), mode == kCube ? 4u * nconf : 0u), 16);
     L.mw = o;     if (weighted && !rows) o = lds_align(o + 8 * block, 16);
     L.mperm = o;  if (anchored && !rows) o = lds_align(o + 4 * block, 16);
+    L.mj = o;     if (mu) o = lds_align(o + 16 * (block + kMaxGroup), 16);
+    L.buf = o;    if (mu) o = lds_align(o + 8 * kMuBuf * (uint32_t)(block / 64), 16);
     L.misc = o;   o = lds_align(o + 384, 16);
     // lanes without a candidate read (and ignore) up to 2 (24 * 24 + 256)
     // bytes past the counter table
@@ -309,6 +314,129 @@ __device__ __forceinline__ void walkp(const WalkP &c, uint32_t nsteps) {
             for (int v = 0; v < kLane; ++v)
                 add_term3<WT>(c, hit[u * kLane + v], ad[u * kLane + v], lo, hi, ng2, r[u * kLane + v]);
         }
+    }
+}
+
+// What the mu counts add: hits go through a buffer in LDS, so that their
+// orientation is worked out on full wavefronts.
+struct WalkMu {
+    uint2 *buf;                   // third vertex; slot | hub << 10 | counters' LDS address << 16
+    const float4 *mj;             // by slot: the spoke's separation from its hub over rmax; its label
+    const int4 *q4, *mq;          // positions, by label; of the group's hubs
+    const double *X, *Y, *Z;
+    const uint32_t *perm;
+    double L, half;
+    float scale, eps;             // a position unit and 4.5 e (see eval_mu) over rmax
+    int nmu;
+    uint32_t i0;                  // the group's first hub
+    uint32_t held;                // hits in the buffer
+};
+
+// The buffer's last n (at most 64 kMuLane) triangles. Whatever the order of the
+// vertices, their plane is the same, so |nz| / |n| is first taken in float32
+// from the separations u and v of j and k from the hub in units of rmax. Their
+// components are off by e, twice the rounding of positions to 2^-32 of the
+// box, and by 2 r of themselves (r = 2^-24; a common factor cancels), so with
+// |.|1 for the sum of magnitudes each component of n is off by less than 5 r
+// |u|1 |v|1 + e (|u|1 + |v|1) + r |n|, and nmu mu by less than 2.8 nmu / |n|
+// times the first two and 6 nmu r for the rest. Where it comes within 1.6
+// times that of a bin edge (some 1e-5 of the triangles) the bin is worked out
+// in float64 from the coordinates in original-index order, as it is defined.
+// Measured on 5e5 clustered points (2e9 triangles, 5 mu bins): 17.5 ms by the
+// hash kernel with every bin in float64, 10.4 so, 9.5 with the hubs' positions
+// in LDS and two triangles a lane, so that their gathers overlap. Bound by
+// the walk's and this code's vector instructions (55% busy) at 16 wavefronts
+// a CU, which the buffers' LDS allows.
+__device__ __forceinline__ void eval_mu(WalkMu &m, uint32_t n) {
+    const uint32_t lane = threadIdx.x & 63u;
+    wave_lds_sync();
+    m.held -= n;
+    uint2 t[kMuLane];
+    int4 qk[kMuLane];
+#pragma unroll
+    for (int s = 0; s < kMuLane; ++s) {
+        t[s] = m.buf[m.held + min(64 * s + lane, n - 1)];
+        qk[s] = m.q4[t[s].x];
+    }
+    const float fmu = (float)m.nmu;
+#pragma unroll
+    for (int s = 0; s < kMuLane; ++s) {
+        const uint32_t hk = (t[s].y >> 10) & 3u;
+        const int4 qi = m.mq[hk];
+        const float4 u = m.mj[t[s].y & 1023u];
+        const float vx = (float)(int)((uint32_t)qk[s].x - (uint32_t)qi.x) * m.scale,
+                    vy = (float)(int)((uint32_t)qk[s].y - (uint32_t)qi.y) * m.scale,
+                    vz = (float)(int)((uint32_t)qk[s].z - (uint32_t)qi.z) * m.scale;
+        const float nx = fmaf(u.y, vz, -(u.z * vy)), ny = fmaf(u.z, vx, -(u.x * vz)), nz = fmaf(u.x, vy, -(u.y * vx));
+        const float rs = __builtin_amdgcn_rsqf(fmaf(nx, nx, fmaf(ny, ny, nz * nz)));
+        const float r = fabsf(nz) * rs * fmu, edge = rintf(r);
+        const float ua = fabsf(u.x) + fabsf(u.y) + fabsf(u.z), va = fabsf(vx) + fabsf(vy) + fabsf(vz);
+        const float margin = fmu * fmaf(rs, fmaf(24.0f * 0x1p-24f * ua, va, m.eps * (ua + va)), 10.0f * 0x1p-24f);
+        uint32_t b = min((uint32_t)r, (uint32_t)m.nmu - 1u);
+        const bool sure = margin < 0.25f && (fabsf(r - edge) > margin || edge < 0.5f || edge > fmu - 0.5f);
+        if (64 * s + lane < n) {
+            if (!sure) {
+                const uint32_t i = m.i0 + hk, j = __float_as_uint(u.w), k = t[s].x;
+                P3x v0{m.X[i], m.Y[i], m.Z[i], m.perm[i]}, v1{m.X[j], m.Y[j], m.Z[j], m.perm[j]},
+                    v2{m.X[k], m.Y[k], m.Z[k], m.perm[k]};
+                order3(v0, v1, v2);
+                b = (uint32_t)mu_bin(min_image(v0.x, v1.x, m.L, m.half), min_image(v0.y, v1.y, m.L, m.half),
+                                     min_image(v0.z, v1.z, m.L, m.half), min_image(v0.x, v2.x, m.L, m.half),
+                                     min_image(v0.y, v2.y, m.L, m.half), min_image(v0.z, v2.z, m.L, m.half), m.nmu);
+            }
+            __hip_atomic_fetch_add((lds_u32 *)(size_t)((t[s].y >> 16) + 4 * b), 1u, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+    wave_lds_sync();
+}
+
+// walkp for mu counts (one step per lane group and pass).
+__device__ __forceinline__ void walkp_mu(const WalkP &c, uint32_t nsteps, WalkMu &m) {
+    const uint32_t sub4 = (threadIdx.x & ((1u << c.slog) - 1u)) * kLane;
+    const uint32_t per = 64u >> c.slog;
+    const uint32_t first = (threadIdx.x & 63u) >> c.slog;
+    const uint32_t pmap = (kNP - 1) << 1, psh = c.shift - 1;
+    auto load = [&](uint32_t base, uint32_t &meta, u32x4_a4 &k4, uint32_t &zb, uint32_t &lim) {
+        const uint32_t i = base + first;
+        const uint2 e = c.step[min(i, nsteps - 1)];
+        const uint32_t cnt = i < nsteps ? e.y & 127u : 0u;
+        meta = e.y;
+        lim = cnt > sub4 ? cnt - sub4 : 0u;
+        const uint32_t pos = e.x + (lim ? sub4 : 0u);
+        k4 = *(gbl_u32x4 *)((gbl_u8 *)c.srow + (pos << 2));
+        zb = *(gbl_u32u *)(c.sbrow + pos);
+    };
+    uint32_t meta, zb, lim;
+    u32x4_a4 k4;
+    load(0, meta, k4, zb, lim);
+    for (uint32_t base = 0; base < nsteps; base += per) {
+        uint32_t meta2, zb2, lim2;
+        u32x4_a4 k42;
+        load(base + per, meta2, k42, zb2, lim2);   // the next pass's rows
+        const uint32_t ptb = (meta >> 16) & (3u << 9);
+        const uint32_t xb = c.xbase + __umul24((meta >> 17) & 255u, c.xmul);
+        const uint32_t sl = ((meta >> 7) & 1023u) | ((meta >> 25) & 3u) << 10;
+        uint32_t y[kLane], ad[kLane];
+#pragma unroll
+        for (int v = 0; v < kLane; ++v) y[v] = *(lds_u16 *)(size_t)(((k4[v] >> psh) & pmap) | ptb);
+#pragma unroll
+        for (int v = 0; v < kLane; ++v) y[v] = *(lds_u8 *)(size_t)((k4[v] & c.pmask) | y[v]);
+#pragma unroll
+        for (int v = 0; v < kLane; ++v)
+            ad[v] = *(lds_u16 *)(size_t)(xb + __umul24(y[v], c.ymul) + (((zb >> (8 * v)) & 255u) << 1));
+#pragma unroll
+        for (int v = 0; v < kLane; ++v) {
+            const bool hit = y[v] != 0u && (uint32_t)v < lim;
+            const uint64_t bal = __ballot(hit);
+            if (hit) m.buf[m.held + lanes_below(bal)] = make_uint2(k4[v], sl | ad[v] << 16);
+            m.held += (uint32_t)__popcll(bal);
+        }
+        while (m.held >= 64 * kMuLane) eval_mu(m, 64 * kMuLane);
+        meta = meta2;
+        zb = zb2;
+        lim = lim2;
+        k4 = k42;
     }
 }
 
@@ -551,10 +679,10 @@ __device__ __forceinline__ void form_group(const C3Args &a, SharedP &S, GroupP &
 // steps in a table of its own and walks them, so that a group of hubs costs
 // four barriers however many steps it has. The first wavefront out of chunks
 // forms the next group while the others finish.
-template <int BLOCK, int WT, bool ANCHORED, bool BATCH, int MODE, bool WIDE, bool LONG>
-__global__ __launch_bounds__(BLOCK, WT && BLOCK < 768 ? 4 : 6) void k_count3p(C3Args a) {
+template <int BLOCK, int WT, bool ANCHORED, bool BATCH, int MODE, bool WIDE, bool LONG, bool MU = false>
+__global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_count3p(C3Args a) {
     extern __shared__ __align__(16) unsigned char sm[];
-    const LayoutP L = layoutp(BLOCK, a.tbytes, a.nconf, a.nb, WT != 0, ANCHORED, MODE, LONG);
+    const LayoutP L = layoutp(BLOCK, a.tbytes, a.nconf, a.nb, WT != 0, ANCHORED, MODE, LONG, MU);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6;
     if (lds_addr(sm) != 0) {   // map and page addresses start at LDS address 0
         if (tid == 0) atomicOr(a.err, 2u);
@@ -575,7 +703,7 @@ __global__ __launch_bounds__(BLOCK, WT && BLOCK < 768 ? 4 : 6) void k_count3p(C3
     for (uint32_t t = tid; t < (L.lut - kPages) / 4; t += BLOCK) ((uint32_t *)(sm + kPages))[t] = 0;   // pages, counters
     if (MODE == kLut)
         for (int t = tid; t < a.nb * a.nb * a.nb; t += BLOCK)
-            ((uint16_t *)(sm + L.lut))[t] = (uint16_t)(L.cnt + a.cfg3[t] * (WT ? 8u : 4u));
+            ((uint16_t *)(sm + L.lut))[t] = (uint16_t)(L.cnt + a.cfg3[t] * (WT ? 8u : MU ? 4u * a.nmu : 4u));
     if (tid == 0) {
         S.cursor = HubCursor();
         S.tcursor = HubCursor();
@@ -602,6 +730,10 @@ __global__ __launch_bounds__(BLOCK, WT && BLOCK < 768 ? 4 : 6) void k_count3p(C3
     c.ymul = (MODE == kCube ? 4 : 2) * a.nb; c.xmul = c.ymul * a.nb;
     c.xbase = (MODE == kCube ? L.cnt : L.lut) - c.ymul;
     c.anchor_lo = a.anchor_lo; c.anchor_hi = a.anchor_hi;
+    WalkMu m;
+    float4 *mj = (float4 *)(sm + L.mj);
+    if (MU)
+        m = WalkMu{(uint2 *)(sm + L.buf) + wid * kMuBuf, mj, a.q4, (const int4 *)(mj + BLOCK), a.X, a.Y, a.Z, a.perm, a.L, a.half, a.qscale, 4.5f * a.qscale, a.nmu, 0, 0};
     uint32_t dirty = 0;   // page bytes in use
 
     for (uint32_t gi = 0;; gi ^= 1u) {
@@ -637,6 +769,10 @@ __global__ __launch_bounds__(BLOCK, WT && BLOCK < 768 ? 4 : 6) void k_count3p(C3
         c.pmask = pmask;
         c.hw = G.hw;
         c.hp = G.hp;
+        if (MU) {
+            m.i0 = i0;
+            if (tid < K) ((int4 *)(mj + BLOCK))[tid] = a.q4[i0 + tid];
+        }
         // spokes of this tile have labels >= jlo; their rows are addressed
         // from rb = rp[jlo]
         const uint32_t jlo = max(i0 + 1, s0);
@@ -765,6 +901,13 @@ __global__ __launch_bounds__(BLOCK, WT && BLOCK < 768 ? 4 : 6) void k_count3p(C3
                                 x = hbinp[beg + sidx];
                                 st = (uint32_t)(rk - rb);
                                 len = (uint32_t)(rp[j + 1] - rk);
+                                if (MU) {
+                                    const int4 qj = a.q4[j], qi = m.mq[hb + hk];
+                                    mj[tid] = make_float4((float)(int)((uint32_t)qj.x - (uint32_t)qi.x) * a.qscale,
+                                                          (float)(int)((uint32_t)qj.y - (uint32_t)qi.y) * a.qscale,
+                                                          (float)(int)((uint32_t)qj.z - (uint32_t)qi.z) * a.qscale,
+                                                          __uint_as_float(j));
+                                }
                                 if (WT) {
                                     ws = a.w[j];
                                     if (!LONG) mw[tid] = ws;
@@ -888,9 +1031,11 @@ __global__ __launch_bounds__(BLOCK, WT && BLOCK < 768 ? 4 : 6) void k_count3p(C3
                                 step[i - w0] = make_uint2(st + off, ey | min(SE, len - off));
                             }
                             wave_lds_sync();
-                            walkp<WT, ANCHORED, MODE, WIDE>(c, min(kWaveSteps, T - w0));
+                            if (MU) walkp_mu(c, min(kWaveSteps, T - w0), m);
+                            else walkp<WT, ANCHORED, MODE, WIDE>(c, min(kWaveSteps, T - w0));
                             wave_lds_sync();
                         }
+                        if (MU && m.held) eval_mu(m, m.held);   // (the next chunk takes the slots)
                     }
                     if (!formed && hb + ks >= K) {
                         uint32_t d = 1;
@@ -941,12 +1086,12 @@ __global__ __launch_bounds__(BLOCK, WT && BLOCK < 768 ? 4 : 6) void k_count3p(C3
     if (lane == 0 && a.probes && probed) atomicAdd(a.probes, (unsigned long long)probed);
 }
 
-template <int B, int WT, bool AN, bool BATCH, int MODE, bool WIDE, bool LONG>
+template <int B, int WT, bool AN, bool BATCH, int MODE, bool WIDE, bool LONG, bool MU = false>
 void launchp_k(Ctx &ctx, hipStream_t s, const C3Args &a, uint32_t lds) {
-    const void *kern = reinterpret_cast<const void *>(&k_count3p<B, WT, AN, BATCH, MODE, WIDE, LONG>);
+    const void *kern = reinterpret_cast<const void *>(&k_count3p<B, WT, AN, BATCH, MODE, WIDE, LONG, MU>);
     if (lds > 65536) GS_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     int per_cu = 0;
-    GS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_count3p<B, WT, AN, BATCH, MODE, WIDE, LONG>, B, lds));
+    GS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_count3p<B, WT, AN, BATCH, MODE, WIDE, LONG, MU>, B, lds));
     if (per_cu < 1) fail(GS_EUNSUPPORTED, "count kernel does not fit a compute unit");
     uint32_t grid = (uint32_t)ctx.n_cu * (uint32_t)per_cu;
     grid = (grid + kNumQueues - 1) / kNumQueues * kNumQueues;
@@ -958,7 +1103,7 @@ void launchp_k(Ctx &ctx, hipStream_t s, const C3Args &a, uint32_t lds) {
     if (LONG && (WT != 0 || AN) && grid > a.rowgroups) grid = a.rowgroups / kNumQueues * kNumQueues;
     if (const char *e = getenv("GS_PGRID")) grid = std::min<uint32_t>(grid, atoi(e));
     if (getenv("GS_PLAN_LOG")) fprintf(stderr, "count3p launch: %d groups per CU, grid %u\n", per_cu, grid);
-    k_count3p<B, WT, AN, BATCH, MODE, WIDE, LONG><<<dim3(grid), dim3(B), lds, s>>>(a);
+    k_count3p<B, WT, AN, BATCH, MODE, WIDE, LONG, MU><<<dim3(grid), dim3(B), lds, s>>>(a);
     GS_HIP(hipGetLastError());
 }
 
@@ -998,7 +1143,7 @@ int env_int(const char *name, int otherwise) {
 }  // namespace
 
 bool planp(const Ctx &ctx, uint32_t maxdeg, int nb, bool weighted, bool anchored, uint64_t n, double mean_row,
-           double cell_points, const Tune3 &tune, PlanP &p) {
+           double cell_points, const Tune3 &tune, PlanP &p, int nmu) {
     if (env_int("GS_PAGED", 1) == 0) return false;
     // overrides of the hash walk's schedule (tests) ask for the hash walk
     for (const char *e : {"GS_MODE3", "GS_PACK", "GS_BLOCK3", "GS_TMAX", "GS_TRUNC", "GS_GLOG"})
@@ -1012,13 +1157,14 @@ bool planp(const Ctx &ctx, uint32_t maxdeg, int nb, bool weighted, bool anchored
     // 1.00 ms at 17 entries a row on 4.2e5 points, 0.93 against 1.05 of it at
     // 30; 0.204 against 0.143 ms at 21 entries on 2e4 points
     if (mean_row < 28.0 && n >= 24000 && env_int("GS_PAGED", 0) == 0 && !getenv("GS_PGLOG")) return false;
-    const int nconf = (int)n_configs(nb);
+    const int nconf = (int)n_configs(nb) * std::max(1, nmu);
     // steps of 16 or 32 entries, whole-wavefront rows from 1000 entries on
     // (weighted, 5.5e4 points: 81 against 91 ms at 1318 a row, 37.3 against
     // 36.8 at 970, 25.5 against 19.9 at 606)
     p.glog = mean_row >= 1000.0 ? 6 : mean_row >= 160.0 ? 5 : 4;
     if (tune.glog > 0) p.glog = std::max(4, std::min(6, tune.glog));
     p.glog = env_int("GS_PGLOG", p.glog);
+    if (nmu) p.glog = std::min(p.glog, 5);
     p.kmax = tune.group > 0 ? std::min(tune.group, kMaxGroup) : kMaxGroup;
     p.kmax = std::max(1, std::min(p.kmax, env_int("GS_GROUP", p.kmax)));
     int best = -1;
@@ -1027,10 +1173,10 @@ bool planp(const Ctx &ctx, uint32_t maxdeg, int nb, bool weighted, bool anchored
         if (tune.block > 0 && blk != tune.block) continue;
         if (getenv("GS_PBLOCK") && blk != env_int("GS_PBLOCK", 256)) continue;
         for (int mode : {kCube, kLut}) {
-            if (mode == kCube && (weighted || anchored || nb > kCubeMaxBins || tune.mode == kLut)) continue;
-            if (mode == kLut && tune.mode == kCube && !weighted && !anchored && nb <= kCubeMaxBins) continue;
-            if (getenv("GS_PMODE") && mode != env_int("GS_PMODE", 0) && !weighted && !anchored) continue;
-            const uint32_t fixed = layoutp(blk, 0, nconf, nb, weighted, anchored, mode, p.glog >= 6).total;
+            if (mode == kCube && (weighted || anchored || nmu || nb > kCubeMaxBins || tune.mode == kLut)) continue;
+            if (mode == kLut && tune.mode == kCube && !weighted && !anchored && !nmu && nb <= kCubeMaxBins) continue;
+            if (getenv("GS_PMODE") && !nmu && mode != env_int("GS_PMODE", 0) && !weighted && !anchored) continue;
+            const uint32_t fixed = layoutp(blk, 0, nconf, nb, weighted, anchored, mode, p.glog >= 6, nmu != 0).total;
             // pages: about 8 bytes per entry of the rows a group holds
             const double rows = p.glog >= 6 ? mean_row : std::max(mean_row, std::min<double>(p.kmax * mean_row, 2.0 * blk));
             const double per = p.glog >= 6 && (weighted || anchored) ? 2.0 : 1.0;   // bytes per label
@@ -1038,7 +1184,8 @@ bool planp(const Ctx &ctx, uint32_t maxdeg, int nb, bool weighted, bool anchored
             const uint32_t most = std::max(least, (uint32_t)(per * 10.0 * std::max<double>(maxdeg, rows)) + 4096u);
             // the counter table holds 16-bit LDS addresses of the (first) counter words
             const uint32_t below = 65536u - kPages - 1024u - (mode == kCube ? 0u : (weighted ? 8u : 4u) * (uint32_t)nconf);
-            const int cap_waves = weighted && blk < 768 ? 16 : 24;
+            if (4ull * nconf + kPages + 4096 >= 65536) continue;
+            const int cap_waves = (weighted && blk < 768) || nmu ? 16 : 24;
             for (int g = cap_waves * 64 / blk; g >= 1; --g) {
                 const int room = (ctx.max_lds / g) / 1280 * 1280 - (int)fixed;
                 if (room < 1024 || (g > 1 && (uint32_t)room < least)) continue;
@@ -1049,7 +1196,7 @@ bool planp(const Ctx &ctx, uint32_t maxdeg, int nb, bool weighted, bool anchored
                     p.mode = mode;
                     p.tbytes = std::min<uint32_t>(std::min<uint32_t>((uint32_t)room, most), below) / 1024 * 1024;
                     if (const char *e = getenv("GS_PTAB")) p.tbytes = std::max(1024, std::min(atoi(e), std::min(room, (int)below))) / 1024 * 1024;
-                    p.lds = layoutp(blk, p.tbytes, nconf, nb, weighted, anchored, mode, p.glog >= 6).total;
+                    p.lds = layoutp(blk, p.tbytes, nconf, nb, weighted, anchored, mode, p.glog >= 6, nmu != 0).total;
                 }
                 break;
             }
@@ -1093,7 +1240,10 @@ void launchp(Ctx &ctx, hipStream_t s, const C3Args &a0, const PlanP &P, bool wei
     // a chunk of spokes fits half the limit
     const uint64_t chunk = (a.maxdeg > 4096 ? 16ull : 64ull) * ((uint64_t)a.maxdeg + (1ull << P.glog));
     a.flush_limit = std::max<uint64_t>(a.flush_limit, 2 * chunk + 2);
-    if (P.block == 768) {   // weighted, unanchored, long rows
+    if (a.nmu) {
+        if (P.block == 512) launchp_k<512, 0, false, false, kLut, false, false, true>(ctx, s, a, P.lds);
+        else launchp_k<256, 0, false, false, kLut, false, false, true>(ctx, s, a, P.lds);
+    } else if (P.block == 768) {   // weighted, unanchored, long rows
         if (wt == 1) launchp_k<768, 1, false, false, kLut, false, true>(ctx, s, a, P.lds);
         else launchp_k<768, 2, false, false, kLut, false, true>(ctx, s, a, P.lds);
     } else if (P.block == 512) {

@@ -24,8 +24,9 @@
 // bin 0. The counter of a triangle is conf(sorted side bins) * nmu + mu bin.
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 
-#include "kern_util.h"
+#include "count3.h"
 
 namespace gsn {
 namespace {
@@ -75,39 +76,6 @@ __host__ __device__ inline LayoutX layoutx(int block, uint32_t H, uint32_t maxde
     L.pb = o;     o = lds_align(o + d, 16);
     L.total = o;
     return L;
-}
-
-// mu bin of the triangle with (minimum-image) edge vectors u = p0->p1 and
-// v = p0->p2.
-__device__ __forceinline__ int mu_bin(double ux, double uy, double uz, double vx, double vy, double vz, int nmu) {
-    const double nx = __dsub_rn(__dmul_rn(uy, vz), __dmul_rn(uz, vy));
-    const double ny = __dsub_rn(__dmul_rn(uz, vx), __dmul_rn(ux, vz));
-    const double nz = __dsub_rn(__dmul_rn(ux, vy), __dmul_rn(uy, vx));
-    const double s = __dadd_rn(__dadd_rn(__dmul_rn(nx, nx), __dmul_rn(ny, ny)), __dmul_rn(nz, nz));
-    const double t = __dmul_rn(__dmul_rn(nz, nz), (double)(nmu * nmu));
-    int m = 0;
-    if (s > 0.0)
-        for (int k = 1; k < nmu; ++k) m += t >= __dmul_rn((double)(k * k), s);
-    return m;
-}
-
-// A vertex: absolute coordinates and original index.
-struct P3x {
-    double x, y, z;
-    uint32_t o;
-};
-
-__device__ __forceinline__ void swapx(P3x &a, P3x &b) {
-    const P3x t = a;
-    a = b;
-    b = t;
-}
-
-// Sort three vertices by original index.
-__device__ __forceinline__ void order3(P3x &a, P3x &b, P3x &c) {
-    if (a.o > b.o) swapx(a, b);
-    if (b.o > c.o) swapx(b, c);
-    if (a.o > b.o) swapx(a, b);
 }
 
 template <int BLOCK, bool WEIGHTED>
@@ -346,6 +314,27 @@ void count3x_run(Ctx &ctx, const Graph &g, int kind, int nmu, uint64_t *hist, ui
     if ((int)L.total > ctx.max_lds)
         fail(GS_EUNSUPPORTED, "restricted triangle kernel LDS footprint too large (" + std::to_string(L.total) +
                                   " bytes)");
+    // the paged triangle kernel where it serves (4.7 / 17.5 ms here against
+    // 2.6 / 9.5 ms, 5e5 clustered points, 15 bins, 5 mu bins)
+    if (count3_paged(ctx, g, weighted, anchored, mu ? nmu : 0)) {
+        const int nconf = (int)n_configs(nb);
+        std::vector<uint64_t> h(mu ? 0 : nconf), w(weighted ? 2 * (size_t)nconf : 0);
+        count3_run(ctx, g, mu ? hist : h.data(), weighted ? w.data() : nullptr, ntri, anchors, nullptr, 0, 0, mu ? nmu : 0);
+        if (!mu) {   // the configurations (b, b, b)
+            *ntri = 0;
+            for (int b = 0; b < nb; ++b) {
+                const int c = rank_a(nb, b) + rank_b(nb, b) + b;
+                hist[b] = h[c];
+                *ntri += h[c];
+                if (weighted) {
+                    wsum[2 * b] = w[2 * c];
+                    wsum[2 * b + 1] = w[2 * c + 1];
+                }
+            }
+        }
+        if (wscale) *wscale = weighted ? weight_scale(g, 3) : 0;
+        return;
+    }
     const size_t woff = ((size_t)ncnt + 1 + 31) / 32 * 32;
     const size_t qoff = weighted ? (woff + 2 * (size_t)ncnt + 31) / 32 * 32 : woff;
     const size_t words = qoff + kQueueWords / 2;
