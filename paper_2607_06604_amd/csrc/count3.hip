@@ -1326,7 +1326,7 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
 }
 
 bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nmu) {
-    if (g.n == 0 || g.n_windows != 1 || g.n_edges >= kWideSpan) return false;
+    if (g.n == 0 || g.n_windows != 1) return false;
     const double mean_row = (double)g.n_edges / (double)g.n;
     if (nmu) {
         // the float32 mu bins take positions in 2^-32 of the box: no wrap
@@ -1337,7 +1337,8 @@ bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nm
     const bool packed = (uint64_t)g.n < (1ull << 24) - 1;
     const Tune3 tune = tuned_for(ctx, tune_key(g.nbins, weighted, packed, g.max_deg, mean_row));
     PlanP p;
-    return planp(ctx, g.max_deg, g.nbins, weighted, anchored, (uint64_t)g.n, mean_row, g.cell_points, tune, p, nmu);
+    return planp(ctx, g.max_deg, g.nbins, weighted, anchored, (uint64_t)g.n, mean_row, g.cell_points, tune, p, nmu) &&
+           (g.n_edges < kWideSpan || p.glog >= 6);
 }
 
 void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64_t *ntri,
@@ -1359,8 +1360,8 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
         for (int w = 0; w < W; ++w) max_rows = std::max<uint64_t>(max_rows, g.win_edge[w + 1] - g.win_edge[w]);
     }
     PlanP PP;
-    const bool paged = max_rows < kWideSpan && planp(ctx, maxdeg, nb, weighted, anchored, (uint64_t)g.n, mean_row,
-                                                     g.cell_points, tune, PP, nmu);
+    const bool paged = planp(ctx, maxdeg, nb, weighted, anchored, (uint64_t)g.n, mean_row, g.cell_points, tune, PP, nmu) &&
+                       (max_rows < kWideSpan || PP.glog >= 6);   // (whole-wavefront rows have 64-bit offsets)
     if (nmu && !paged) fail(GS_EUNSUPPORTED, "mu bins need the paged table here");
     const Plan3 P = paged ? Plan3() : plan3(ctx, maxdeg, nb, weighted, anchored, (uint64_t)g.n, mean_row, tune);
     const int ntiles = W * (W + 1) / 2;
@@ -1632,8 +1633,8 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
     // the built-in schedule, spelled out
     Tune3 cur;
     PlanP PP;
-    const bool paged = g.n_edges < kWideSpan &&
-                       planp(ctx, g.max_deg, nb, weighted, false, (uint64_t)g.n, mean_row, g.cell_points, Tune3(), PP);
+    const bool paged = planp(ctx, g.max_deg, nb, weighted, false, (uint64_t)g.n, mean_row, g.cell_points, Tune3(), PP) &&
+                       (g.n_edges < kWideSpan || PP.glog >= 6);
     if (paged) {
         cur.block = PP.block;
         cur.glog = PP.glog;

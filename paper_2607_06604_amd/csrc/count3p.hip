@@ -159,12 +159,14 @@ __device__ __forceinline__ double max_f64(double x, double y) {
     return r;
 }
 
-// A lane's double as a wavefront-uniform value.
+// A lane's value as a wavefront-uniform one.
+__device__ __forceinline__ uint64_t lane_u64(uint64_t x, int lane) {
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(x >> 32), lane);
+    return ((uint64_t)hi << 32) | lo;
+}
 __device__ __forceinline__ double lane_f64(double x, int lane) {
-    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane);
-    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+    return __longlong_as_double((long long)lane_u64((uint64_t)__double_as_longlong(x), lane));
 }
 
 // What the walk over one step table reads.
@@ -688,6 +690,11 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
         if (tid == 0) atomicOr(a.err, 2u);
         return;
     }
+    // offsets of spoke rows from the group's first: 64 bits cost a long row
+    // nothing (2.5e5 points, BAO scale: 592 ms, as before), and its graph may
+    // hold 2^32 entries (2e6 points, 7.2e9 entries: 4.81 s, against 9.21 by
+    // the hash table, which took such graphs)
+    using RowOfs = typename std::conditional<LONG, uint64_t, uint32_t>::type;
     constexpr bool RANK = LONG && (WT != 0 || ANCHORED);   // 16-bit page entries with ranks; lone hubs
     uint16_t *pt = (uint16_t *)sm;
     uint32_t *ptk = (uint32_t *)sm;   // RANK: page address | row position of its first entry << 16
@@ -891,7 +898,8 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
                         const uint32_t sidx = (ch << csl) + lane;
                         const uint32_t hk = (sidx >= ofs1) + (sidx >= ofs2) + (sidx >= ofs3);
                         const uint32_t next = hk == 0 ? ofs1 : hk == 1 ? ofs2 : hk == 2 ? ofs3 : kEmptyKey;
-                        uint32_t st = 0, len = 0, x = 0, pj = 0;
+                        RowOfs st = 0;
+                        uint32_t len = 0, x = 0, pj = 0;
                         double ws = 0.0;
                         // (the last entry of a row is no spoke)
                         if (lane < (1u << csl) && sidx + 1 < D && sidx + 1 != next) {
@@ -899,7 +907,7 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
                             if (j >= s0 && j < s1 && j < khi) {
                                 const uint64_t rk = rp[j];
                                 x = hbinp[beg + sidx];
-                                st = (uint32_t)(rk - rb);
+                                st = (RowOfs)(rk - rb);
                                 len = (uint32_t)(rp[j + 1] - rk);
                                 if (MU) {
                                     const int4 qj = a.q4[j], qi = m.mq[hb + hk];
@@ -977,8 +985,8 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
                             live &= live - 1;
                             // a spoke's row, from a 64-byte boundary of the labels
                             auto start = [&](int l) {
-                                const uint32_t b = __builtin_amdgcn_readlane(st, l);
-                                const uint32_t skip = (al + b) & 15u;
+                                const uint64_t b = lane_u64(st, l);
+                                const uint32_t skip = (al + (uint32_t)b) & 15u;
                                 return RowPass{c.srow + b - skip, c.sbrow + b - skip, skip,
                                                skip + __builtin_amdgcn_readlane(len, l)};
                             };
@@ -1028,7 +1036,7 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
                             const uint32_t lo = max(t0, w0), hi = min(t1, w0 + kWaveSteps);
                             for (uint32_t i = lo; i < hi; ++i) {
                                 const uint32_t off = (i - t0) << selog;
-                                step[i - w0] = make_uint2(st + off, ey | min(SE, len - off));
+                                step[i - w0] = make_uint2((uint32_t)st + off, ey | min(SE, len - off));
                             }
                             wave_lds_sync();
                             if (MU) walkp_mu(c, min(kWaveSteps, T - w0), m);
