@@ -15,13 +15,15 @@ workloads ride along in the same line under "configs" (fewer steps each):
 the 1e6-point clustered 3pCF, the 2e5-point parity 4pCF and the serving
 stream of 256 catalogues.
 
-Rooflines. The triangle count is bound by instruction issue on its hash
-probes (measured traffic is a fraction of HBM bandwidth), so its roofline is
-candidates probed per second against the attainable probe rate that the
-library's probe microbenchmark measures on this GPU with the same table
-size, load, bin count, hit rate and weighting; the HBM share (measured
-traffic against 8 TB/s and against a measured stream copy), the LDS-atomic
-histogram ceiling and the merge-walk byte model are reported beside it. The
+Rooflines. The triangle count looks candidates up in a label table in LDS and
+adds its hits to counters in LDS, so its roofline is triangles per second
+against the attainable rate of those additions alone, which the library's
+microbenchmark measures on this GPU for the same bin count and weighting.
+Where the schedule is the hash table's (rows that the label table does not
+serve), it is candidates probed per second against the measured probe rate
+for the same table size, load, bin count, hit rate and weighting. The HBM
+share (measured traffic against 8 TB/s and against a measured stream copy)
+and the merge-walk byte model are reported beside it. The
 parity count is float64 work: 120 operations per 4-clique against the
 published 78.6 TFLOP/s. cpu_baseline = the CPU oracle on a bounded sample
 of the same catalogue (anchor ranges spread over it), on the host's cores.
@@ -207,17 +209,19 @@ def run_workload(gsn, ctx, name, steps, warmup, tune=True, windows=0, with_cpu=T
         ops = FP64_OPS_PER_CLIQUE * tuples
         tflops = ops / (count_kernel_ms / 1e3) / 1e12 if count_kernel_ms > 0 else 0.0
         roofline = {"bound": "alu", "achieved": round(tflops, 3), "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
-                    "frac": round(tflops / FP64_PEAK_TFLOPS, 4), "traffic": traffic, "kernel": "k_count4",
+                    "frac": round(tflops / FP64_PEAK_TFLOPS, 4), "traffic": traffic, "kernel": "k_count4m",
                     "fp64_ops_per_clique": FP64_OPS_PER_CLIQUE, "avg_launch_ms": round(avg_launch_ms, 4),
                     "hbm_measured_GBs": round(traffic / (avg_launch_ms / 1e3) / 1e9, 1) if traffic else None}
     else:
         probes_per_count = probes // steps
         achieved = probes_per_count / (count_kernel_ms / 1e3) / 1e9 if count_kernel_ms > 0 else 0.0
         hit = tuples / max(1, probes_per_count)
-        log2h, keys, block = plan_table(info, t)
         weighted = kind == "w3pcf"
-        peak = ctx.ceiling_probe(w.nbins, log2h, keys, min(1.0, max(1e-6, hit)), weighted=weighted,
-                                 probe=True, block=block) / 1e9
+        paged = int(t.table_log2) == 0
+        # (the histogram ceiling reads no table: any size serves)
+        log2h, keys, block = (10, 512, int(t.block)) if paged else plan_table(info, t)
+        peak = 0.0 if paged else ctx.ceiling_probe(w.nbins, log2h, keys, min(1.0, max(1e-6, hit)), weighted=weighted,
+                                                   probe=True, block=block) / 1e9
         hist_peak = ctx.ceiling_probe(w.nbins, log2h, keys, 1.0, weighted=weighted, probe=False,
                                       block=block) / 1e9
         tri_rate = tuples / (count_kernel_ms / 1e3) / 1e9 if count_kernel_ms > 0 else 0.0
@@ -227,20 +231,27 @@ def run_workload(gsn, ctx, name, steps, warmup, tune=True, windows=0, with_cpu=T
             gbs = traffic / (avg_launch_ms / 1e3) / 1e9
             hbm = {"measured_GBs": round(gbs, 1), "frac_of_peak": round(gbs / HBM_PEAK_GBS, 4),
                    "frac_of_copy": round(gbs / ceil["copy_GBs"], 4) if ceil else None}
-        roofline = {"bound": "alu", "achieved": round(achieved, 2), "peak": round(peak, 2), "unit": "Gprobe/s",
-                    "frac": round(achieved / peak, 4) if peak > 0 else None, "traffic": traffic,
-                    "kernel": "k_count3", "avg_launch_ms": round(avg_launch_ms, 4),
-                    "launches_per_count": launches // max(steps, 1),
-                    "probes_per_count": probes_per_count, "hit_rate": round(hit, 4),
+        if paged:
+            rate = {"bound": "lds", "achieved": round(tri_rate, 2), "peak": round(hist_peak, 2), "unit": "Gtuples/s",
+                    "frac": round(tri_rate / hist_peak, 4) if hist_peak > 0 else None, "kernel": "k_count3p",
+                    "Gcandidates_per_s": round(achieved, 2),
+                    "peak_source": "gs_ceiling_probe: counter additions only, %d bins, %s, %d threads per group"
+                                   % (w.nbins, "weighted" if weighted else "unweighted", block)}
+        else:
+            rate = {"bound": "alu", "achieved": round(achieved, 2), "peak": round(peak, 2), "unit": "Gprobe/s",
+                    "frac": round(achieved / peak, 4) if peak > 0 else None, "kernel": "k_count3",
                     "peak_source": "gs_ceiling_probe: table 2^%d slots, %d keys, %d bins, hit rate %.3f, %s, "
                                    "%d threads per group" % (log2h, keys, w.nbins, hit,
-                                                             "weighted" if weighted else "unweighted", block),
+                                                             "weighted" if weighted else "unweighted", block)}
+        roofline = {**rate, "traffic": traffic, "avg_launch_ms": round(avg_launch_ms, 4),
+                    "launches_per_count": launches // max(steps, 1),
+                    "probes_per_count": probes_per_count, "hit_rate": round(hit, 4),
                     "hbm": hbm,
                     "lds_hist": {"achieved_Gtuples_s": round(tri_rate, 2), "peak_Gtuples_s": round(hist_peak, 2),
                                  "frac": round(tri_rate / hist_peak, 4) if hist_peak > 0 else None},
                     "merge_walk_model": {"alg_bytes_per_count": alg_bytes, "GBs": round(merge_gbs, 1),
                                          "note": "2.5 B x sum of squared degrees: the bytes a two-pointer merge "
-                                                 "walk over both forward half lists would read; the hash probes "
+                                                 "walk over both forward half lists would read; the table lookups "
                                                  "read each spoke row once per hub from L2, so this is a model, "
                                                  "not a bound"}}
     out = {
