@@ -484,7 +484,8 @@ __device__ uint64_t block_scan_u64(uint64_t v, uint64_t *wtot, uint64_t &total) 
 template <class TI>
 __global__ __launch_bounds__(kBlock) void k_scan_tiles(const TI *__restrict__ in, uint64_t n,
                                                         uint64_t *__restrict__ out,
-                                                        uint64_t *__restrict__ tile_sums) {
+                                                        uint64_t *__restrict__ tile_sums,
+                                                        uint64_t *__restrict__ total_out) {
     __shared__ uint64_t wtot[kBlock / 64];
     uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanItems;
     uint64_t v[kScanItems];
@@ -499,51 +500,70 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiles(const TI *__restrict__ in
         if (base + k < n) out[base + k] = pre;
         pre += v[k];
     }
-    if (threadIdx.x == 0) tile_sums[blockIdx.x] = total;
+    if (threadIdx.x == 0) {
+        if (gridDim.x > 1) {
+            tile_sums[blockIdx.x] = total;
+        } else {   // a single tile: the scan is done
+            out[n] = total;
+            if (total_out) *total_out = total;
+        }
+    }
 }
 
 __global__ void k_scan_add(uint64_t *__restrict__ out, uint64_t n,
-                           const uint64_t *__restrict__ tile_off) {
+                           const uint64_t *__restrict__ tile_off, uint64_t ntiles,
+                           uint64_t *__restrict__ total_out) {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) out[i] += tile_off[i / kScanTile];
+    if (i == n) {
+        out[n] = tile_off[ntiles];
+        if (total_out) *total_out = tile_off[ntiles];
+    }
 }
 
-__global__ void k_set_total(uint64_t *out, uint64_t n, const uint64_t *tile_off, uint64_t ntiles,
-                            const uint64_t *tile_sums) {
-    out[n] = tile_off[ntiles - 1] + tile_sums[ntiles - 1];
+// What a build starts from: flags (words 0..7 zero; words 8.. the least and
+// the largest weight's bits) and empty cells.
+__global__ void k_build_init(uint64_t *__restrict__ flags, uint32_t *__restrict__ count, uint32_t ncell) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < ncell) count[i] = 0;
+    if (i < 8) flags[i] = i == 4 ? ~0ull : 0ull;
 }
 
 inline unsigned grid_for(uint64_t n, int block = kBlock) { return (unsigned)((n + block - 1) / block); }
 
-// Exclusive scan of n values into out[0..n]; out[n] = total.
+// Exclusive scan of n values into out[0..n]; out[n] = total (and *total_out,
+// if given). One launch up to kScanTile values, three up to its square: on
+// small catalogues the build is bound by its launches (4 to 5 us each).
 // Temporaries come from the building context's cache (reused only by later
 // work on the same stream) or, without one, are freed after a synchronize.
 template <class TI>
-void scan(const TI *in, uint64_t n, uint64_t *out, hipStream_t s, const std::shared_ptr<DevPool> &pool) {
-    if (n == 0) {
-        k_fill_u64<<<1, 1, 0, s>>>(out, 1, 0);
-        return;
+void scan(const TI *in, uint64_t n, uint64_t *out, hipStream_t s, const std::shared_ptr<DevPool> &pool,
+          uint64_t *total_out = nullptr) {
+    uint64_t ntiles = std::max<uint64_t>(1, (n + kScanTile - 1) / kScanTile);
+    DevBuf sums, offs;
+    if (ntiles > 1) {
+        sums.alloc(sizeof(uint64_t) * ntiles, pool);
+        offs.alloc(sizeof(uint64_t) * (ntiles + 1), pool);
     }
-    uint64_t ntiles = (n + kScanTile - 1) / kScanTile;
-    DevBuf sums(sizeof(uint64_t) * ntiles, pool), offs(sizeof(uint64_t) * (ntiles + 1), pool);
-    k_scan_tiles<TI><<<(unsigned)ntiles, kBlock, 0, s>>>(in, n, out, sums.as<uint64_t>());
+    k_scan_tiles<TI><<<(unsigned)ntiles, kBlock, 0, s>>>(in, n, out, sums.as<uint64_t>(), total_out);
     GS_HIP(hipGetLastError());
     if (ntiles > 1) {
         scan<uint64_t>(sums.as<uint64_t>(), ntiles, offs.as<uint64_t>(), s, pool);
-        k_scan_add<<<grid_for(n), kBlock, 0, s>>>(out, n, offs.as<uint64_t>());
-    } else {
-        k_fill_u64<<<1, 1, 0, s>>>(offs.as<uint64_t>(), 1, 0);
+        k_scan_add<<<grid_for(n + 1), kBlock, 0, s>>>(out, n, offs.as<uint64_t>(), ntiles, total_out);
+        GS_HIP(hipGetLastError());
     }
-    k_set_total<<<1, 1, 0, s>>>(out, n, offs.as<uint64_t>(), ntiles, sums.as<uint64_t>());
-    GS_HIP(hipGetLastError());
     if (!pool) GS_HIP(hipStreamSynchronize(s));  // sums/offs are freed on return
 }
 
-// Chunks of at most `chunk` labels per cell.
+// Chunks of at most `chunk` labels per cell; the cells' counters are cleared
+// for the scatter.
 __global__ void k_chunk_count(const uint64_t *__restrict__ cstart, uint32_t ncell, uint32_t chunk,
-                              uint32_t *__restrict__ nch) {
+                              uint32_t *__restrict__ nch, uint32_t *__restrict__ count) {
     const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < ncell) nch[c] = (uint32_t)((cstart[c + 1] - cstart[c] + chunk - 1) / chunk);
+    if (c < ncell) {
+        nch[c] = (uint32_t)((cstart[c + 1] - cstart[c] + chunk - 1) / chunk);
+        count[c] = 0;
+    }
 }
 
 // The cell of every chunk.
@@ -648,10 +668,7 @@ void build_begin(Ctx &ctx, Graph &g, const double *xyz, const double *w, BuildJo
     DevBuf &cstart = job.cstart, &cellL = job.cellL;
     job.nc = nc;
     uint32_t *fl = flags.as<uint32_t>();
-    k_fill_u32<<<1, 64, 0, s>>>(fl, 8, 0);
-    k_fill_u64<<<1, 64, 0, s>>>(flags.as<uint64_t>() + 4, 1, ~0ull);  // wmin bits
-    k_fill_u64<<<1, 64, 0, s>>>(flags.as<uint64_t>() + 5, 1, 0);      // wmax bits
-    k_fill_u32<<<grid_for(ncell), kBlock, 0, s>>>(count.as<uint32_t>(), ncell, 0);
+    k_build_init<<<grid_for(ncell), kBlock, 0, s>>>(flags.as<uint64_t>(), count.as<uint32_t>(), (uint32_t)ncell);
     k_cells<<<grid_for(n), kBlock, 0, s>>>(dxyz, n, g.box, nc, cell_of.as<uint32_t>(),
                                            count.as<uint32_t>(), fl);
     if (weighted)
@@ -666,13 +683,12 @@ void build_begin(Ctx &ctx, Graph &g, const double *xyz, const double *w, BuildJo
         job.grid = (uint64_t)n / job.chunk + ncell;   // at most one partial chunk per cell
         job.gcell.alloc(sizeof(uint32_t) * job.grid, ctx.pool);
         k_chunk_count<<<grid_for(ncell), kBlock, 0, s>>>(cstart.as<uint64_t>(), (uint32_t)ncell, job.chunk,
-                                                          nch.as<uint32_t>());
+                                                          nch.as<uint32_t>(), count.as<uint32_t>());
         scan<uint32_t>(nch.as<uint32_t>(), ncell, job.chpref.as<uint64_t>(), s, ctx.pool);
         k_chunk_cells<<<grid_for(ncell), kBlock, 0, s>>>(job.chpref.as<uint64_t>(), (uint32_t)ncell,
                                                           job.gcell.as<uint32_t>());
         GS_HIP(hipGetLastError());
     }
-    k_fill_u32<<<grid_for(ncell), kBlock, 0, s>>>(count.as<uint32_t>(), ncell, 0);
     k_scatter<<<grid_for(n), kBlock, 0, s>>>(cell_of.as<uint32_t>(), n, cstart.as<uint64_t>(),
                                              count.as<uint32_t>(), order.as<uint32_t>());
     k_rank<<<grid_for(n), kBlock, 0, s>>>(order.as<uint32_t>(), cell_of.as<uint32_t>(),
@@ -701,19 +717,18 @@ void build_begin(Ctx &ctx, Graph &g, const double *xyz, const double *w, BuildJo
     ea.maxdeg = fl + 1;
     k_edges<false><<<(unsigned)job.grid, kBlock, 0, s>>>(ea);
     GS_HIP(hipGetLastError());
-    scan<uint32_t>(deg.as<uint32_t>(), n, g.row_ptr.as<uint64_t>(), s, ctx.pool);
+    scan<uint32_t>(deg.as<uint32_t>(), n, g.row_ptr.as<uint64_t>(), s, ctx.pool, flags.as<uint64_t>() + 6);
 
     struct {
         uint32_t f[8];
-        uint64_t wmin, wmax;
+        uint64_t wmin, wmax, edges;
     } hf;
-    uint64_t E = 0;
     GS_HIP(hipEventRecord(ctx.ev[1], s));
     GS_HIP(hipMemcpyAsync(&hf, fl, sizeof hf, hipMemcpyDeviceToHost, s));
-    GS_HIP(hipMemcpyAsync(&E, g.row_ptr.as<uint64_t>() + n, sizeof E, hipMemcpyDeviceToHost, s));
     GS_HIP(hipStreamSynchronize(s));
     if (hf.f[0] & 1u) fail(GS_EINVAL, "coordinate outside [0, box) or NaN");
     if (hf.f[0] & 2u) fail(GS_EINVAL, "weights must be finite and nonzero");
+    const uint64_t E = hf.edges;
     g.n_edges = E;
     g.max_deg = hf.f[1];
     if (weighted) {
