@@ -315,8 +315,11 @@ void count3x_run(Ctx &ctx, const Graph &g, int kind, int nmu, uint64_t *hist, ui
         fail(GS_EUNSUPPORTED, "restricted triangle kernel LDS footprint too large (" + std::to_string(L.total) +
                                   " bytes)");
     // the paged triangle kernel where it serves (4.7 / 17.5 ms here against
-    // 2.6 / 9.5 ms, 5e5 clustered points, 15 bins, 5 mu bins)
-    if (count3_paged(ctx, g, weighted, anchored, mu ? nmu : 0)) {
+    // 2.6 / 9.5 ms, 5e5 clustered points, 15 bins, 5 mu bins; 364 / 926 us
+    // against 354 / 680 on 5e4 points, but 203 / 276 against 210 / 306 on 2e4
+    // and 171 / 316 against 222 / 453 on 5e3, where its tiles, tables and
+    // many more counters to hand in outweigh the walk; GS_PAGED=1: tests)
+    if ((g.n >= 40000 || getenv("GS_PAGED")) && count3_paged(ctx, g, weighted, anchored, mu ? nmu : 0)) {
         const int nconf = (int)n_configs(nb);
         std::vector<uint64_t> h(mu ? 0 : nconf), w(weighted ? 2 * (size_t)nconf : 0);
         count3_run(ctx, g, mu ? hist : h.data(), weighted ? w.data() : nullptr, ntri, anchors, nullptr, 0, 0, mu ? nmu : 0);
