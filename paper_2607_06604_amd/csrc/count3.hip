@@ -1187,7 +1187,9 @@ __global__ void k_box_units(const double *__restrict__ C, uint32_t n, double sca
 }
 
 uint64_t flush_limit_for(uint32_t maxdeg, uint64_t per_chunk_factor) {
-    // GS_FLUSH_LIMIT lowers the flush threshold (exercises the flush path)
+    // GS_FLUSH_LIMIT lowers the flush threshold (exercises the flush path) down
+    // to what the hash walk adds between two looks; the paged walk (factor 0)
+    // raises it to its own least
     const char *fl = getenv("GS_FLUSH_LIMIT");
     uint64_t v = fl ? strtoull(fl, nullptr, 10) : 0xFFFFFFFFull;
     if (v < per_chunk_factor * (maxdeg + 1) || v > 0xFFFFFFFFull) v = 0xFFFFFFFFull;
@@ -1303,7 +1305,7 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
     a.maxdeg = maxdeg;
     a.tmax = P.tmax;
     a.tcap = P.tcap;
-    a.flush_limit = flush_limit_for(maxdeg, P.block);
+    a.flush_limit = flush_limit_for(maxdeg, paged ? 0 : P.block);
     a.queue = (uint32_t *)(dv + qoff);
     a.err = (uint32_t *)(dv + (size_t)ng * per);
     a.cfg3 = (const uint16_t *)(dv + coff);
@@ -1367,9 +1369,9 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     const int ntiles = W * (W + 1) / 2;
     int kused = 1;          // hubs per group of the launches (reported in the timings)
 
-    // device staging: hist | wsum | ntri | error word | probes | queue sets,
-    // one per tile (256-byte aligned)
-    const size_t qoff = (3 * (size_t)nconf + 3 + 31) / 32 * 32;
+    // device staging: hist | wsum | ntri | error word | probes | flushes | queue
+    // sets, one per tile (256-byte aligned)
+    const size_t qoff = (3 * (size_t)nconf + 4 + 31) / 32 * 32;
     const std::vector<uint16_t> cfg = config_table(nb);   // | configuration table
     const size_t coff = qoff + (size_t)ntiles * kQueueWords / 2;
     // | hub tile bounds | block costs
@@ -1400,7 +1402,7 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     a.anchor_hi = anchored ? (uint32_t)std::min<uint64_t>(anchors->hi, 0xFFFFFFFFull) : 0;
     a.wmul = weighted ? std::ldexp(1.0, weight_scale(g, 3)) : 1.0;
     a.wgen = weighted && (g.wneg || wide_terms(g, 3));
-    a.flush_limit = flush_limit_for(maxdeg, P.block);
+    a.flush_limit = flush_limit_for(maxdeg, paged ? 0 : P.block);
     a.hist = dv;
     a.wsum = dv + nconf;
     a.ntri = dv + 3 * (size_t)nconf;
@@ -1411,6 +1413,7 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     if (const char *es = getenv("GS_WIDE_SPAN")) a.wspan = std::max<uint64_t>(strtoull(es, nullptr, 10), 1);
     a.wspan = std::min<uint64_t>(kWideSpan, std::max<uint64_t>(a.wspan, (uint64_t)maxdeg + 1));
     a.probes = dv + 3 * (size_t)nconf + 2;
+    a.flushes = (uint32_t *)(dv + 3 * (size_t)nconf + 3);
     a.cfg3 = (const uint16_t *)(dv + coff);
     uint32_t *queues = (uint32_t *)(dv + qoff);
     uint32_t *tbounds = (uint32_t *)(dv + toff);
@@ -1575,7 +1578,7 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
         }
     }
     GS_HIP(hipEventRecord(ctx.ev[3], s));
-    std::vector<unsigned long long> h(3 * (size_t)nconf + 3);
+    std::vector<unsigned long long> h(3 * (size_t)nconf + 4);
     GS_HIP(hipMemcpyAsync(h.data(), dv, h.size() * 8, hipMemcpyDeviceToHost, s));
     GS_HIP(hipEventRecord(ctx.ev[1], s));
     GS_HIP(hipStreamSynchronize(s));
@@ -1591,6 +1594,9 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     ctx.t.kernel_ms = kms;
     ctx.t.kernel_launches = g.n > 0 ? (uint64_t)ntiles : 0;
     ctx.t.probes = h[3 * (size_t)nconf + 2];
+    if (paged && getenv("GS_PLAN_LOG"))
+        fprintf(stderr, "count3p: %u flushes in mid-count, %u put off\n", (uint32_t)h[3 * (size_t)nconf + 3],
+                (uint32_t)(h[3 * (size_t)nconf + 3] >> 32));
     ctx.t.table_log2 = paged ? 0 : P.log2h;
     ctx.t.block = paged ? PP.block : P.block;
     ctx.t.group = kused;

@@ -1057,7 +1057,7 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
                     // the walked candidates bound every counter; the fullest
                     // one is a better bound
                     unsigned long long now = a.flush_limit;
-                    if (WT && a.refresh) {
+                    if (WT) {
                         uint32_t top = 0;
                         for (int b = tid; b < a.nconf; b += BLOCK)
                             top = max(top, (uint32_t)(((unsigned long long *)(sm + L.cnt))[b] >> kCntShift));
@@ -1065,10 +1065,12 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
                         __syncthreads();
                         now = __builtin_amdgcn_readfirstlane(S.top);
                     }
-                    if (now >= a.flush_limit / 2) {
+                    const bool full = now >= a.flush_limit / 2;
+                    if (full) {
                         flushp<BLOCK, WT, MODE>(a, L, sm, hout, tout);
                         now = 0;
                     }
+                    if (tid == 0 && a.flushes) atomicAdd(a.flushes + (full ? 0 : 1), 1u);
                     __syncthreads();
                     if (tid == 0) {
                         S.acc = now;
@@ -1237,14 +1239,8 @@ void launchp(Ctx &ctx, hipStream_t s, const C3Args &a0, const PlanP &P, bool wei
     a.inorder = P.glog >= 6;
     if (const char *e = getenv("GS_PORDER")) a.inorder = atoi(e);
     const int wt = !weighted ? 0 : a.wgen ? 2 : 1;
-    // fields of the weighted counters (see the head of this file); forced
-    // flushes (GS_FLUSH_LIMIT) skip the look at the fullest counter
-    a.refresh = 0;
-    if (wt) {
-        const uint64_t lim = wt == 1 ? 1ull << 21 : 1ull << 20;
-        a.refresh = a.flush_limit >= lim;
-        a.flush_limit = std::min(a.flush_limit, lim);
-    }
+    // fields of the weighted counters (see the head of this file)
+    if (wt) a.flush_limit = std::min<uint64_t>(a.flush_limit, wt == 1 ? 1ull << 21 : 1ull << 20);
     // a chunk of spokes fits half the limit
     const uint64_t chunk = (a.maxdeg > 4096 ? 16ull : 64ull) * ((uint64_t)a.maxdeg + (1ull << P.glog));
     a.flush_limit = std::max<uint64_t>(a.flush_limit, 2 * chunk + 2);
