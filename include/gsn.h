@@ -292,7 +292,9 @@ int gs_count_3pcf_batch(gs_ctx *ctx, const gs_graph *const *graphs, int ng, uint
  * from the built-in choice and changing one parameter at a time while that
  * helps; the fastest is kept in the context for graphs of g's shape (bin
  * count, weighting, label width, and the scale of the largest and the mean
- * forward degree), and every later count of such a graph in this context
+ * forward degree) that the same kernel counts -- what a count cannot take of
+ * it (768 threads with anchors) is then its built-in choice --
+ * and every later count of such a graph in this context
  * (gs_count_3pcf, gs_count_3pcf_batch, and requests served after the
  * context's first gs_submit, which takes the schedules tuned before it) uses
  * it. Not thread-safe against concurrent counts on the same context.
@@ -306,7 +308,9 @@ typedef struct {
     int32_t table;       /* step table entries per fill                          */
     int32_t counters;    /* 0: rank arithmetic, 1: table of counter addresses,   */
                          /* 2: per-(x,y,z) counters folded at flush              */
-    int32_t hash_load;   /* hub hash table load bound: 5 (1/2) or 7 (0.7)         */
+    int32_t hash_load;   /* hub hash table load bound: 5 (1/2) or 7 (0.7); 0:    */
+                         /* the paged label table counts (128 step entries,       */
+                         /* rows always cut)                                      */
     int32_t truncate;    /* 1: spoke rows cut at the hub row's largest label     */
     int32_t trials;      /* schedules timed                                      */
     double sample_ms;    /* chosen schedule on the sample (kernel time)          */

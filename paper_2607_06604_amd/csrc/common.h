@@ -143,11 +143,15 @@ struct Server;
 // Result staging shared by the count entry points of one context.
 // A triangle-count schedule (-1: the built-in choice): work-group size,
 // entries per step (log2), hubs per group, step table entries, counter mode,
-// hash table load bound, spoke-row truncation.
+// hash table load bound, spoke-row truncation; and the kernel it is for (the
+// two take different values: 768 threads go with long steps only in one of
+// them, the other has no table of steps to size).
+enum { kHash3 = 0, kPaged3 = 1 };
 struct Tune3 {
     int block = -1, glog = -1, group = -1, tmax = -1, mode = -1;
     int hload = 0;   // hash table load bound: 5 (1/2), 7 (0.7), 0 built-in
     int trunc = -1;  // spoke rows cut at the hub row's largest label: 0, 1, -1 built-in
+    int kernel = -1; // kHash3, kPaged3 or either
 };
 
 struct Ctx {

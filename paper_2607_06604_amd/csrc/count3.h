@@ -71,6 +71,10 @@ struct C3Args {
     uint32_t ntiles;
 };
 
+// 32-bit offsets of spoke rows from a hub's first: bytes below 2^30 entries,
+// entries below 2^32.
+constexpr uint64_t kNarrowSpan = 1ull << 30;
+constexpr uint64_t kWideSpan = 1ull << 32;
 constexpr int kLutMaxBins = 24;          // nb^3 u16 table up to 27 KB
 constexpr int kCubeMaxBins = 16;         // nb^3 u32 counters up to 16 KB
 constexpr int kMaxGroup = 4;             // hubs per group: two bits in a step entry
@@ -91,11 +95,22 @@ struct PlanP {
     uint32_t lds = 0;
 };
 
-// The schedule for a graph of the given degrees, or false where the paged
-// table does not serve (then the hash table does).
-// nmu: mu bins (else 0).
-bool planp(const Ctx &ctx, uint32_t maxdeg, int nb, bool weighted, bool anchored, uint64_t n, double mean_row,
-           double cell_points, const Tune3 &tune, PlanP &p, int nmu = 0);
+// What a schedule depends on.
+struct Shape3 {
+    uint32_t maxdeg = 0;
+    int nb = 0;
+    bool weighted = false, anchored = false;
+    uint64_t n = 0;          // points (the largest catalogue of a batch)
+    double mean_row = 0;     // forward entries per point
+    double cell_points = 0;  // points per cell of the build's grid
+    uint64_t max_rows = 0;   // entries that the spoke rows of one launch span
+    int nmu = 0;             // mu bins (else 0)
+};
+
+// The schedule for a graph of that shape, or false where the paged table does
+// not serve (then the hash table does). A tuned value that this count cannot
+// take (768 threads with anchors, say) gives way to the built-in choice.
+bool planp(const Ctx &ctx, const Shape3 &g, const Tune3 &tune, PlanP &p);
 // rows: device memory the launch may need (taken on first use; held by the
 // caller until the launch has completed).
 void launchp(Ctx &ctx, hipStream_t s, const C3Args &a, const PlanP &P, bool weighted, bool anchored, bool batch,

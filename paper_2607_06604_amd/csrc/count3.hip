@@ -41,10 +41,9 @@ __host__ __device__ constexpr int unroll3(bool weighted, bool anchored) {
     return weighted && !anchored ? kUnroll3W : kUnroll3;
 }
 // Spoke rows of one hub are addressed by 32-bit offsets from the hub's
-// first spoke row: byte offsets (loads with a scalar base) below 2^30
-// entries, entry offsets with 64-bit addresses (WIDE launches) below 2^32.
-constexpr uint64_t kNarrowSpan = 1ull << 30;
-constexpr uint64_t kWideSpan = 1ull << 32;
+// first spoke row: byte offsets (loads with a scalar base) below kNarrowSpan
+// entries, entry offsets with 64-bit addresses (WIDE launches) below
+// kWideSpan.
 
 // LDS layout of one work group (byte offsets). The configuration table and
 // the counters come first so that their byte addresses fit 16 bits.
@@ -921,13 +920,14 @@ uint64_t tune_key(int nb, bool weighted, bool packed, uint32_t maxdeg, double me
     return (uint64_t)nb | (uint64_t)weighted << 8 | (uint64_t)packed << 9 | lmax << 10 | lmean << 20;
 }
 
-// The tuned schedule of the nearest shape with the same bin count, weighting
-// and label width, if its degree scales are within a factor two of key's.
-Tune3 tuned_for(const Ctx &ctx, uint64_t key) {
+// The kernel's tuned schedule of the nearest shape with the same bin count,
+// weighting and label width, if its degree scales are within a factor two of
+// key's.
+Tune3 tuned_for(const Ctx &ctx, uint64_t key, int kernel) {
     Tune3 best;
     long bestd = 5;
     for (const auto &kv : ctx.tuned) {
-        if ((kv.first & 0x3FF) != (key & 0x3FF)) continue;
+        if ((kv.first & 0x3FF) != (key & 0x3FF) || kv.second.kernel != kernel) continue;
         const long dmax = std::labs((long)((kv.first >> 10) & 0x3FF) - (long)((key >> 10) & 0x3FF));
         const long dmean = std::labs((long)(kv.first >> 20) - (long)(key >> 20));
         if (dmax <= 2 && dmean <= 2 && dmax + dmean < bestd) {
@@ -1244,12 +1244,17 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
     }
     const double mean_row = nvirt ? (double)sum_e / (double)nvirt : 0.0;
     const bool packed = max_n < (1ull << 24) - 1;
-    const Tune3 tune = tuned_for(ctx, tune_key(nb, false, packed, maxdeg, mean_row));
-    double cells = 0;   // points per cell, averaged over the points
-    for (int g = 0; g < ng; ++g) cells += gs[g]->cell_points * (double)gs[g]->n;
-    if (nvirt) cells /= (double)nvirt;
+    const uint64_t key = tune_key(nb, false, packed, maxdeg, mean_row);
+    Shape3 shape;
+    shape.maxdeg = maxdeg;
+    shape.nb = nb;
+    shape.n = max_n;
+    shape.mean_row = mean_row;
+    for (int g = 0; g < ng; ++g)   // points per cell, averaged over the points
+        shape.cell_points += gs[g]->cell_points * ((double)gs[g]->n / (double)std::max<uint64_t>(nvirt, 1));
     PlanP PP;
-    const bool paged = planp(ctx, maxdeg, nb, false, false, max_n, mean_row, cells, tune, PP);
+    const bool paged = planp(ctx, shape, tuned_for(ctx, key, kPaged3), PP);
+    const Tune3 tune = tuned_for(ctx, key, kHash3);
     const Plan3 P = paged ? Plan3() : plan3(ctx, maxdeg, nb, false, false, max_n, mean_row, tune);
     b.ng = ng;
     b.nconf = nconf;
@@ -1327,20 +1332,36 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
     GS_HIP(hipEventRecord(b.done, s));
 }
 
+namespace {
+Shape3 shape_of(const Graph &g, bool weighted, bool anchored, int nmu = 0) {
+    Shape3 h;
+    h.maxdeg = g.max_deg;
+    h.nb = g.nbins;
+    h.weighted = weighted;
+    h.anchored = anchored;
+    h.n = (uint64_t)g.n;
+    h.mean_row = g.n ? (double)g.n_edges / (double)g.n : 0.0;
+    h.cell_points = g.cell_points;
+    h.max_rows = g.n_edges;
+    for (int w = 0; g.n_windows > 1 && w < g.n_windows; ++w)
+        h.max_rows = std::max<uint64_t>(w ? h.max_rows : 1, g.win_edge[w + 1] - g.win_edge[w]);
+    h.nmu = nmu;
+    return h;
+}
+}  // namespace
+
 bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nmu) {
     if (g.n == 0 || g.n_windows != 1) return false;
-    const double mean_row = (double)g.n_edges / (double)g.n;
     if (nmu) {
         // the float32 mu bins take positions in 2^-32 of the box: no wrap
         // among a triangle's vertices, and rounding well below theirs
         if (weighted || anchored || wide_rows(g.n_edges)) return false;
         if (!(4.0 * g.rmax * (1.0 + 1e-9) < g.box && g.box <= 256.0 * g.rmax)) return false;
     }
-    const bool packed = (uint64_t)g.n < (1ull << 24) - 1;
-    const Tune3 tune = tuned_for(ctx, tune_key(g.nbins, weighted, packed, g.max_deg, mean_row));
+    const Shape3 h = shape_of(g, weighted, anchored, nmu);
+    const bool packed = h.n < (1ull << 24) - 1;
     PlanP p;
-    return planp(ctx, g.max_deg, g.nbins, weighted, anchored, (uint64_t)g.n, mean_row, g.cell_points, tune, p, nmu) &&
-           (g.n_edges < kWideSpan || p.glog >= 6);
+    return planp(ctx, h, tuned_for(ctx, tune_key(h.nb, weighted, packed, h.maxdeg, h.mean_row), kPaged3), p);
 }
 
 void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64_t *ntri,
@@ -1350,20 +1371,16 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     const bool weighted = wsum != nullptr;
     const bool anchored = anchors != nullptr;
     if (anchored && (anchors->lo > anchors->hi)) fail(GS_EINVAL, "anchor range lo > hi");
-    const uint32_t maxdeg = g.max_deg;
-    const double mean_row = g.n ? (double)g.n_edges / (double)g.n : 0.0;
+    const Shape3 shape = shape_of(g, weighted, anchored, nmu);
+    const uint32_t maxdeg = shape.maxdeg;
+    const double mean_row = shape.mean_row;
     const bool packed = (uint64_t)g.n < (1ull << 24) - 1;
-    const Tune3 tune = force ? *force : tuned_for(ctx, tune_key(nb, weighted, packed, maxdeg, mean_row));
+    const uint64_t key = tune_key(nb, weighted, packed, maxdeg, mean_row);
     const int W = g.n_windows;
     // the paged table where it serves, else the hash table
-    uint64_t max_rows = g.n_edges;   // entries the spoke rows of one launch span
-    if (W > 1) {
-        max_rows = 1;
-        for (int w = 0; w < W; ++w) max_rows = std::max<uint64_t>(max_rows, g.win_edge[w + 1] - g.win_edge[w]);
-    }
     PlanP PP;
-    const bool paged = planp(ctx, maxdeg, nb, weighted, anchored, (uint64_t)g.n, mean_row, g.cell_points, tune, PP, nmu) &&
-                       (max_rows < kWideSpan || PP.glog >= 6);   // (whole-wavefront rows have 64-bit offsets)
+    const bool paged = planp(ctx, shape, force ? *force : tuned_for(ctx, key, kPaged3), PP);
+    const Tune3 tune = force ? *force : tuned_for(ctx, key, kHash3);
     if (nmu && !paged) fail(GS_EUNSUPPORTED, "mu bins need the paged table here");
     const Plan3 P = paged ? Plan3() : plan3(ctx, maxdeg, nb, weighted, anchored, (uint64_t)g.n, mean_row, tune);
     const int ntiles = W * (W + 1) / 2;
@@ -1637,19 +1654,22 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
     };
 
     // the built-in schedule, spelled out
+    const Shape3 shape = shape_of(g, weighted, false);
+    auto resolved = [&](const Tune3 &t, Tune3 &r) {   // the schedule that the paged kernel runs for t
+        PlanP p;
+        if (!planp(ctx, shape, t, p)) return false;
+        r = Tune3();
+        r.kernel = kPaged3;
+        r.block = p.block;
+        r.glog = p.glog;
+        r.mode = p.mode;
+        r.group = p.kmax;
+        return true;
+    };
     Tune3 cur;
-    PlanP PP;
-    const bool paged = planp(ctx, g.max_deg, nb, weighted, false, (uint64_t)g.n, mean_row, g.cell_points, Tune3(), PP) &&
-                       (g.n_edges < kWideSpan || PP.glog >= 6);
-    if (paged) {
-        cur.block = PP.block;
-        cur.glog = PP.glog;
-        cur.tmax = 128;   // (fixed)
-        cur.mode = PP.mode;
-        cur.hload = 5;   // (no hash table, no truncation switch)
-        cur.trunc = 1;
-        cur.group = PP.kmax;
-    } else {
+    const bool paged = resolved(Tune3(), cur);
+    if (!paged) {
+        cur.kernel = kHash3;
         const Plan3 P0 = plan3(ctx, g.max_deg, nb, weighted, false, (uint64_t)g.n, mean_row, Tune3());
         cur.block = P0.block;
         cur.glog = P0.glog;
@@ -1685,7 +1705,14 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
         len = next;
     }
     double best = t0;
+    std::vector<Tune3> timed{cur};   // (paged: what one launch has shown is not timed again)
     auto consider = [&](Tune3 t) {
+        if (paged) {
+            if (!resolved(t, t)) return;
+            for (const Tune3 &o : timed)
+                if (o.block == t.block && o.glog == t.glog && o.mode == t.mode && o.group == t.group) return;
+            timed.push_back(t);
+        }
         const double ms = trial(t, lo, hi);
         if (ms < 0.98 * best) {
             best = ms;
@@ -1709,6 +1736,7 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
             if (gl < (paged ? 4 : 0) || gl > 6) continue;
             Tune3 t = cur;
             t.glog = gl;
+            if (paged) t.block = t.group = -1;   // (as they go with these steps)
             consider(t);
         }
         // hubs per group
@@ -1744,7 +1772,7 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
     const uint64_t key = tune_key(nb, weighted, packed, g.max_deg, mean_row);
     bool found = false;
     for (auto &kv : ctx.tuned)
-        if (kv.first == key) {
+        if (kv.first == key && kv.second.kernel == cur.kernel) {
             kv.second = cur;
             found = true;
         }
@@ -1753,10 +1781,10 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
         out->block = cur.block;
         out->step_log2 = cur.glog;
         out->group = cur.group;
-        out->table = cur.tmax;
+        out->table = paged ? 128 : cur.tmax;
         out->counters = cur.mode;
-        out->hash_load = cur.hload;
-        out->truncate = cur.trunc;
+        out->hash_load = paged ? 0 : cur.hload;
+        out->truncate = paged ? 1 : cur.trunc;
         out->trials = trials;
         out->sample_ms = best;
         out->default_ms = t0;

@@ -1152,66 +1152,75 @@ int env_int(const char *name, int otherwise) {
 
 }  // namespace
 
-bool planp(const Ctx &ctx, uint32_t maxdeg, int nb, bool weighted, bool anchored, uint64_t n, double mean_row,
-           double cell_points, const Tune3 &tune, PlanP &p, int nmu) {
-    if (env_int("GS_PAGED", 1) == 0) return false;
+bool planp(const Ctx &ctx, const Shape3 &g, const Tune3 &tune, PlanP &p) {
+    if (env_int("GS_PAGED", 1) == 0 || tune.kernel == kHash3) return false;
     // overrides of the hash walk's schedule (tests) ask for the hash walk
     for (const char *e : {"GS_MODE3", "GS_PACK", "GS_BLOCK3", "GS_TMAX", "GS_TRUNC", "GS_GLOG"})
         if (getenv(e)) return false;
-    if (nb > kLutMaxBins || maxdeg > 16384 || n >= (1ull << 29)) return false;
+    const int nb = g.nb, nmu = g.nmu;
+    const bool weighted = g.weighted, anchored = g.anchored;
+    const uint32_t maxdeg = g.maxdeg;
+    const double mean_row = g.mean_row;
+    if (nb > kLutMaxBins || maxdeg > 16384 || g.n >= (1ull << 29)) return false;
     // a row's labels must be dense enough in its cells: about 6.4 labels per
     // entry when the cells are rmax wide
-    if (13.5 * cell_points > 64.0 * (mean_row + 1.0)) return false;
+    if (13.5 * g.cell_points > 64.0 * (mean_row + 1.0)) return false;
     // the hash walk's finer steps (down to one entry) still win on short rows,
     // unless the count is so small that starting it decides: 0.80 against
     // 1.00 ms at 17 entries a row on 4.2e5 points, 0.93 against 1.05 of it at
     // 30; 0.204 against 0.143 ms at 21 entries on 2e4 points
-    if (mean_row < 28.0 && n >= 24000 && env_int("GS_PAGED", 0) == 0 && !getenv("GS_PGLOG")) return false;
+    if (mean_row < 28.0 && g.n >= 24000 && env_int("GS_PAGED", 0) == 0 && !getenv("GS_PGLOG")) return false;
     const int nconf = (int)n_configs(nb) * std::max(1, nmu);
     // steps of 16 or 32 entries, whole-wavefront rows from 1000 entries on
     // (weighted, 5.5e4 points: 81 against 91 ms at 1318 a row, 37.3 against
-    // 36.8 at 970, 25.5 against 19.9 at 606)
+    // 36.8 at 970, 25.5 against 19.9 at 606); only those have 64-bit offsets
+    const bool far = g.max_rows >= kWideSpan;
     p.glog = mean_row >= 1000.0 ? 6 : mean_row >= 160.0 ? 5 : 4;
-    if (tune.glog > 0) p.glog = std::max(4, std::min(6, tune.glog));
+    if (tune.glog > 0 && !(far && tune.glog < 6)) p.glog = std::max(4, std::min(6, tune.glog));
     p.glog = env_int("GS_PGLOG", p.glog);
     if (nmu) p.glog = std::min(p.glog, 5);
+    if (far && p.glog < 6) return false;
     p.kmax = tune.group > 0 ? std::min(tune.group, kMaxGroup) : kMaxGroup;
     p.kmax = std::max(1, std::min(p.kmax, env_int("GS_GROUP", p.kmax)));
     int best = -1;
-    for (int blk : {256, 512, 768}) {
-        if (blk == 768 && (!weighted || anchored || p.glog < 6)) continue;
-        if (tune.block > 0 && blk != tune.block) continue;
-        if (getenv("GS_PBLOCK") && blk != env_int("GS_PBLOCK", 256)) continue;
-        for (int mode : {kCube, kLut}) {
-            if (mode == kCube && (weighted || anchored || nmu || nb > kCubeMaxBins || tune.mode == kLut)) continue;
-            if (mode == kLut && tune.mode == kCube && !weighted && !anchored && !nmu && nb <= kCubeMaxBins) continue;
-            if (getenv("GS_PMODE") && !nmu && mode != env_int("GS_PMODE", 0) && !weighted && !anchored) continue;
-            const uint32_t fixed = layoutp(blk, 0, nconf, nb, weighted, anchored, mode, p.glog >= 6, nmu != 0).total;
-            // pages: about 8 bytes per entry of the rows a group holds
-            const double rows = p.glog >= 6 ? mean_row : std::max(mean_row, std::min<double>(p.kmax * mean_row, 2.0 * blk));
-            const double per = p.glog >= 6 && (weighted || anchored) ? 2.0 : 1.0;   // bytes per label
-            const uint32_t least = (uint32_t)(per * 8.0 * rows) + 2048u;
-            const uint32_t most = std::max(least, (uint32_t)(per * 10.0 * std::max<double>(maxdeg, rows)) + 4096u);
-            // the counter table holds 16-bit LDS addresses of the (first) counter words
-            const uint32_t below = 65536u - kPages - 1024u - (mode == kCube ? 0u : (weighted ? 8u : 4u) * (uint32_t)nconf);
-            if (4ull * nconf + kPages + 4096 >= 65536) continue;
-            const int cap_waves = (weighted && blk < 768) || nmu ? 16 : 24;
-            for (int g = cap_waves * 64 / blk; g >= 1; --g) {
-                const int room = (ctx.max_lds / g) / 1280 * 1280 - (int)fixed;
-                if (room < 1024 || (g > 1 && (uint32_t)room < least)) continue;
-                const int waves = g * blk / 64;
-                if (waves > best) {
-                    best = waves;
-                    p.block = blk;
-                    p.mode = mode;
-                    p.tbytes = std::min<uint32_t>(std::min<uint32_t>((uint32_t)room, most), below) / 1024 * 1024;
-                    if (const char *e = getenv("GS_PTAB")) p.tbytes = std::max(1024, std::min(atoi(e), std::min(room, (int)below))) / 1024 * 1024;
-                    p.lds = layoutp(blk, p.tbytes, nconf, nb, weighted, anchored, mode, p.glog >= 6, nmu != 0).total;
+    auto search = [&](int block, int only) {   // (-1: any)
+        for (int blk : {256, 512, 768}) {
+            if (blk == 768 && (!weighted || anchored || p.glog < 6)) continue;
+            if (block > 0 && blk != block) continue;
+            if (getenv("GS_PBLOCK") && blk != env_int("GS_PBLOCK", 256)) continue;
+            for (int mode : {kCube, kLut}) {
+                if (mode == kCube && (weighted || anchored || nmu || nb > kCubeMaxBins || only == kLut)) continue;
+                if (mode == kLut && only == kCube && !weighted && !anchored && !nmu && nb <= kCubeMaxBins) continue;
+                if (getenv("GS_PMODE") && !nmu && mode != env_int("GS_PMODE", 0) && !weighted && !anchored) continue;
+                const uint32_t fixed = layoutp(blk, 0, nconf, nb, weighted, anchored, mode, p.glog >= 6, nmu != 0).total;
+                // pages: about 8 bytes per entry of the rows a group holds
+                const double rows = p.glog >= 6 ? mean_row : std::max(mean_row, std::min<double>(p.kmax * mean_row, 2.0 * blk));
+                const double per = p.glog >= 6 && (weighted || anchored) ? 2.0 : 1.0;   // bytes per label
+                const uint32_t least = (uint32_t)(per * 8.0 * rows) + 2048u;
+                const uint32_t most = std::max(least, (uint32_t)(per * 10.0 * std::max<double>(maxdeg, rows)) + 4096u);
+                // the counter table holds 16-bit LDS addresses of the (first) counter words
+                const uint32_t below = 65536u - kPages - 1024u - (mode == kCube ? 0u : (weighted ? 8u : 4u) * (uint32_t)nconf);
+                if (4ull * nconf + kPages + 4096 >= 65536) continue;
+                const int cap_waves = (weighted && blk < 768) || nmu ? 16 : 24;
+                for (int gr = cap_waves * 64 / blk; gr >= 1; --gr) {
+                    const int room = (ctx.max_lds / gr) / 1280 * 1280 - (int)fixed;
+                    if (room < 1024 || (gr > 1 && (uint32_t)room < least)) continue;
+                    const int waves = gr * blk / 64;
+                    if (waves > best) {
+                        best = waves;
+                        p.block = blk;
+                        p.mode = mode;
+                        p.tbytes = std::min<uint32_t>(std::min<uint32_t>((uint32_t)room, most), below) / 1024 * 1024;
+                        if (const char *e = getenv("GS_PTAB")) p.tbytes = std::max(1024, std::min(atoi(e), std::min(room, (int)below))) / 1024 * 1024;
+                        p.lds = layoutp(blk, p.tbytes, nconf, nb, weighted, anchored, mode, p.glog >= 6, nmu != 0).total;
+                    }
+                    break;
                 }
-                break;
             }
         }
-    }
+    };
+    search(tune.block, tune.mode);
+    if (best < 0) search(-1, -1);
     if (best < 0) return false;
     if (getenv("GS_PLAN_LOG"))
         fprintf(stderr, "count3p plan: maxdeg %u mean_row %.1f block %d glog %d mode %d group %d table %u lds %u waves/CU %d\n",
