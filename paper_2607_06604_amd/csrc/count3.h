@@ -91,6 +91,7 @@ struct PlanP {
     int glog = 4;          // entries per step = 2^glog (4 to 6)
     int mode = kLut;
     int kmax = kMaxGroup;  // hubs per group at most
+    bool inorder = false;  // hubs go out one at a time in label order, not by tiles
     uint32_t tbytes = 0;   // bytes of the label table's pages
     uint32_t lds = 0;
 };

@@ -1265,7 +1265,7 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
     const std::vector<uint16_t> cfg = config_table(nb);
     const size_t coff = qoff + kQueueWords / 2;
     // | hub tile bounds | block costs
-    const bool use_tiles = tiles_enabled();
+    const bool use_tiles = tiles_enabled() && !(paged && PP.inorder);
     const TilePlan tp = tile_plan(ctx, nvirt);
     const size_t toff = coff + (cfg.size() + 3) / 4;
     const size_t poff = toff + (tp.T() + 2) / 2;    // | hub cost prefix | chunk costs
@@ -1392,7 +1392,7 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     const std::vector<uint16_t> cfg = config_table(nb);   // | configuration table
     const size_t coff = qoff + (size_t)ntiles * kQueueWords / 2;
     // | hub tile bounds | block costs
-    const bool use_tiles = tiles_enabled();
+    const bool use_tiles = tiles_enabled() && !(paged && PP.inorder);
     uint64_t max_hubs = 1;
     for (int w = 0; w < W; ++w) max_hubs = std::max<uint64_t>(max_hubs, W == 1 ? g.n : g.win[w + 1] - g.win[w]);
     const TilePlan tp = tile_plan(ctx, max_hubs);

@@ -1181,7 +1181,8 @@ bool planp(const Ctx &ctx, const Shape3 &g, const Tune3 &tune, PlanP &p) {
     if (nmu) p.glog = std::min(p.glog, 5);
     if (far && p.glog < 6) return false;
     p.kmax = tune.group > 0 ? std::min(tune.group, kMaxGroup) : kMaxGroup;
-    p.kmax = std::max(1, std::min(p.kmax, env_int("GS_GROUP", p.kmax)));
+    p.kmax = p.glog >= 6 ? 1 : std::max(1, std::min(p.kmax, env_int("GS_GROUP", p.kmax)));
+    p.inorder = env_int("GS_PORDER", p.glog >= 6) != 0;
     int best = -1;
     auto search = [&](int block, int only) {   // (-1: any)
         for (int blk : {256, 512, 768}) {
@@ -1233,7 +1234,7 @@ void launchp(Ctx &ctx, hipStream_t s, const C3Args &a0, const PlanP &P, bool wei
     C3Args a = a0;
     a.glog = P.glog;
     a.mode = P.mode;
-    a.kmax = P.glog >= 6 && (weighted || anchored) ? 1 : P.kmax;
+    a.kmax = P.kmax;
     a.group_cap = 2ull * P.block;
     if (P.glog >= 6 && (weighted || anchored)) {
         // packed hub rows, one per work group that can be resident
@@ -1245,8 +1246,7 @@ void launchp(Ctx &ctx, hipStream_t s, const C3Args &a0, const PlanP &P, bool wei
         a.rowgroups = (uint32_t)groups;
     }
     a.tbytes = P.tbytes;
-    a.inorder = P.glog >= 6;
-    if (const char *e = getenv("GS_PORDER")) a.inorder = atoi(e);
+    a.inorder = P.inorder;
     const int wt = !weighted ? 0 : a.wgen ? 2 : 1;
     // fields of the weighted counters (see the head of this file)
     if (wt) a.flush_limit = std::min<uint64_t>(a.flush_limit, wt == 1 ? 1ull << 21 : 1ull << 20);

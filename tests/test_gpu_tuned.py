@@ -52,3 +52,19 @@ def test_anchored_counts_after_tuning_long_rows(monkeypatch, n):
         assert same(c.count_3pcf(g, weighted=True, anchors=an), first)
         assert c.timings().table_log2 > 0
         g.free()
+
+
+def test_long_rows_report_lone_hubs(monkeypatch):
+    """Whole-wavefront rows take hubs one at a time: the timings say so."""
+    import paper_2607_06604_amd as gsn
+    x, w = clump(1_500, 803), synth.uniform_values(1_500, 0.5, 1.0, 804)
+    monkeypatch.setenv("GS_PGLOG", "6")
+    with gsn.Context(0) as c:
+        for weights in (w, None):
+            g = c.build_graph(x, L, 0.0, RMAX, NB, weights=weights)
+            for an in (None, (10, 900)):
+                print("lone hubs", weights is not None, an, flush=True)
+                c.count_3pcf(g, weighted=weights is not None, anchors=an)
+                t = c.timings()
+                assert t.table_log2 == 0 and t.group == 1
+            g.free()
