@@ -1476,9 +1476,16 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
             a.h1 = std::min<uint32_t>(sample_hi, (uint32_t)g.n);
         }
         a.queue = queues;
-        // (few hubs: the three tile kernels cost more than the balance gains,
-        // 1.13 against 1.38 ms for an estimate on 3000 + 3000 points)
-        if (use_tiles && !(paged && a.h1 - a.h0 < 12288)) {
+        // (few hubs: the three tile kernels cost more than the balance gains.
+        // Without tiles and with, as multiples of the hash walk's time, which
+        // has them: 2000 points 0.58 and 0.74, clustered 0.62 and 0.85; 3500:
+        // 0.72 and 0.77, 0.75 and 0.86; 8000: 0.91 and 0.75, 0.87 and 0.85,
+        // and worst, at 2 to 10 entries a row, 1.24 and 1.08. Between, the row
+        // decides: 5000 points of 5 entries 0.95 and 0.81, clustered 0.88 and
+        // 0.87, of 40 entries 0.69 and 0.64, clustered 0.72 and 0.82; 1.13
+        // against 1.38 ms for an estimate on 3000 + 3000 points)
+        const uint32_t hubs = a.h1 - a.h0;
+        if (use_tiles && !(paged && (hubs < 5000 || (hubs < 8000 && mean_row >= 30.0)))) {
             const TilePlan t1 = tile_plan(ctx, a.h1 - a.h0);
             enqueue_tiles(s, t1, a.rp, nullptr, 0, a.h0, a.h1, hpre, ctot, tbounds);
             a.tiles = tbounds;
