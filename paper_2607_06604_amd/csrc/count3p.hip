@@ -1152,6 +1152,37 @@ int env_int(const char *name, int otherwise) {
 
 }  // namespace
 
+namespace {
+// Mean row from which the paged table counts faster than the hash walk, whose
+// steps go down to one entry. Times as multiples of the hash walk's, uniform
+// and clustered catalogues (8e5 points: uniform).
+// Small counts are decided by their start: at 5 to 25 entries 0.72 to 0.79 on
+// 18000 and 22000 points (weighted and anchored up to 1.05, from 18 bins on
+// weighted up to 1.08), still 0.74 to 0.87 on 26000 and 32000, but weighted
+// and anchored ones up to 1.08 on 40000, and any up to 1.19 on 60000 to
+// 250000. Anchors leave few hubs to share that start: on 5000 points and more
+// 1.01 to 1.14 at 2 entries, 0.75 to 1.02 from 4 on, but where the rows are
+// uneven up to 1.10 at 8 to 10 (weighted 1.18 at 10, 1.10 at 12, 1.08 at 15).
+// Large counts: up to 17 bins 1.03 to 1.23 at 28 entries, 0.92 to 1.04 at 36;
+// anchored 1.35 and 1.18, 1.0 to 1.03 at 42. From 18 bins on the counters and
+// their address table, which the hash walk has no more of, leave less room
+// for work groups than shorter rows would fill: 20 bins 1.40 at 28, 1.12 at
+// 55, 0.88 at 75; 18 bins weighted 1.61, 1.23 and 0.95; 24 bins 1.49, 1.33
+// and 1.20 at 85 (0.87 at 110), weighted 0.94 at 28 (the hash walk then has
+// one work group per CU), weighted and anchored 1.41 at 36, 0.94 at 75.
+double least_row(const Shape3 &g) {
+    if (g.n < 24000 && !(g.weighted && g.nb > 17)) {
+        if (!g.anchored || g.n < 5000) return 0.0;
+        const bool uneven = (double)g.maxdeg > 2.0 * g.mean_row + 12.0;
+        return !uneven ? 3.0 : g.weighted ? 16.0 : 11.0;
+    }
+    if (g.nb <= 17) return g.anchored ? 42.0 : 36.0;
+    if (g.nb <= 22) return 70.0;
+    if (g.weighted) return g.anchored ? 70.0 : 36.0;
+    return g.anchored ? 100.0 : 110.0;
+}
+}  // namespace
+
 bool planp(const Ctx &ctx, const Shape3 &g, const Tune3 &tune, PlanP &p) {
     if (env_int("GS_PAGED", 1) == 0 || tune.kernel == kHash3) return false;
     // overrides of the hash walk's schedule (tests) ask for the hash walk
@@ -1165,13 +1196,12 @@ bool planp(const Ctx &ctx, const Shape3 &g, const Tune3 &tune, PlanP &p) {
     // a row's labels must be dense enough in its cells: about 6.4 labels per
     // entry when the cells are rmax wide
     if (13.5 * g.cell_points > 64.0 * (mean_row + 1.0)) return false;
-    // the hash walk's finer steps (down to one entry) still win on short rows,
-    // unless the count is so small that starting it decides: 0.80 against
-    // 1.00 ms at 17 entries a row on 4.2e5 points, 0.93 against 1.05 of it at
-    // 30; 0.204 against 0.143 ms at 21 entries on 2e4 points
-    if (mean_row < 28.0 && g.n >= 24000 && env_int("GS_PAGED", 0) == 0 && !getenv("GS_PGLOG")) return false;
+    // (GS_PAGED, GS_PGLOG: any row, for tests)
+    if (mean_row < least_row(g) && env_int("GS_PAGED", 0) == 0 && !getenv("GS_PGLOG")) return false;
     const int nconf = (int)n_configs(nb) * std::max(1, nmu);
-    // steps of 16 or 32 entries, whole-wavefront rows from 1000 entries on
+    // steps of 16 or 32 entries (the latter 1.00 to 1.08 times the former's
+    // time at 80 a row, 0.94 to 1.04 at 160, 0.80 to 1.03 at 200, 0.83 to 0.99
+    // at 260; 2e4 to 4e5 points), whole-wavefront rows from 1000 entries on
     // (weighted, 5.5e4 points: 81 against 91 ms at 1318 a row, 37.3 against
     // 36.8 at 970, 25.5 against 19.9 at 606); only those have 64-bit offsets
     const bool far = g.max_rows >= kWideSpan;
@@ -1207,7 +1237,12 @@ bool planp(const Ctx &ctx, const Shape3 &g, const Tune3 &tune, PlanP &p) {
                     const int room = (ctx.max_lds / gr) / 1280 * 1280 - (int)fixed;
                     if (room < 1024 || (gr > 1 && (uint32_t)room < least)) continue;
                     const int waves = gr * blk / 64;
-                    if (waves > best) {
+                    // on a tie the smaller group, but the larger where hubs are few
+                    // and long, so that the last ones end sooner: 700 entries, 16 bins,
+                    // weighted, 14.1 ms by 256 threads and 9.1 by 512 on 15000 points
+                    // (12.3 by the hash walk), 18.9 and 19.1 on 40000; 8 bins 67.6
+                    // and 77 on 150000
+                    if (waves > best || (waves == best && mean_row >= 500.0 && p.glog < 6 && g.n < 128ull * ctx.n_cu)) {
                         best = waves;
                         p.block = blk;
                         p.mode = mode;
