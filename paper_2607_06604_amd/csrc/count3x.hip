@@ -292,6 +292,34 @@ void launchx_k(Ctx &ctx, const XArgs &a, uint32_t lds, bool w, bool an) {
     else an ? launchx<KIND, false, true>(ctx, a, lds) : launchx<KIND, false, false>(ctx, a, lds);
 }
 
+// Whether the paged triangle count beats this file's kernel at a restricted
+// count. Times as multiples of this kernel's. An equilateral count takes the
+// whole paged count for its diagonal, with the exact term of every triangle
+// when weighted, where this kernel drops a candidate of another bin unprobed;
+// so the count must be large enough to outweigh the paged one's tables (3e6
+// edges: 0.88 at most on 6e4 points at 50 entries and 3e4 at 110, but 1.05 on
+// 6e4 at 35 and 15000 at 170 with 16 bins), and past 16 bins, where the paged
+// kernel's counters cost it work groups, rows long: 20 bins 1.08 at 35
+// entries on 3e5 points and 0.78 at 75, 24 bins 1.15 and 0.98; weighted 20
+// bins 1.50 at 35, 1.02 at 110, 0.87 at 170; weighted 24 bins 1.40 at 170,
+// 1.32 at 300, 0.86 at 600. (5e5 clustered points, 15 bins: 4.7 to 2.6 ms.)
+// Where it is taken so: 0.62 on average, weighted 0.77, worst 0.96.
+// mu counts: 17.5 to 9.5 ms there with 5 mu bins; 0.75 at 35 entries on 6e4
+// points, 1.03 on 41000. While counters and address table together take 14
+// to 40 KB they cost the paged kernel work groups, this one none: 1.17 to
+// 1.36 at 35 entries, 1.0 to 1.16 at 50, 1.06 at 65, 0.90 at 80.
+bool paged_pays(const Graph &g, int nmu, bool weighted, bool anchored) {
+    const int nb = g.nbins;
+    const double row = g.n ? (double)g.n_edges / (double)g.n : 0.0;
+    if (g.n < 40000) return false;
+    if (nmu) {
+        const int64_t lds = 4 * n_configs(nb) * nmu + 2 * (int64_t)nb * nb * nb;
+        return g.n_edges >= 2000000 && (lds < 14000 || lds > 40000 || row >= 80.0);
+    }
+    if (g.n_edges < 3000000) return false;
+    return nb <= 16 || row >= (!weighted ? 100.0 : nb <= 22 ? 170.0 : 500.0);
+}
+
 }  // namespace
 
 void count3x_run(Ctx &ctx, const Graph &g, int kind, int nmu, uint64_t *hist, uint64_t *wsum, int *wscale,
@@ -314,12 +342,9 @@ void count3x_run(Ctx &ctx, const Graph &g, int kind, int nmu, uint64_t *hist, ui
     if ((int)L.total > ctx.max_lds)
         fail(GS_EUNSUPPORTED, "restricted triangle kernel LDS footprint too large (" + std::to_string(L.total) +
                                   " bytes)");
-    // the paged triangle kernel where it serves (4.7 / 17.5 ms here against
-    // 2.6 / 9.5 ms, 5e5 clustered points, 15 bins, 5 mu bins; 364 / 926 us
-    // against 354 / 680 on 5e4 points, but 203 / 276 against 210 / 306 on 2e4
-    // and 171 / 316 against 222 / 453 on 5e3, where its tiles, tables and
-    // many more counters to hand in outweigh the walk; GS_PAGED=1: tests)
-    if ((g.n >= 40000 || getenv("GS_PAGED")) && count3_paged(ctx, g, weighted, anchored, mu ? nmu : 0)) {
+    // the paged triangle kernel where it serves and pays (GS_PAGED=1: where it serves, for tests)
+    if ((paged_pays(g, mu ? nmu : 0, weighted, anchored) || getenv("GS_PAGED")) && count3_paged(ctx, g, weighted, anchored, mu ? nmu : 0)) {
+        const Timings last = ctx.t;
         const int nconf = (int)n_configs(nb);
         std::vector<uint64_t> h(mu ? 0 : nconf), w(weighted ? 2 * (size_t)nconf : 0);
         count3_run(ctx, g, mu ? hist : h.data(), weighted ? w.data() : nullptr, ntri, anchors, nullptr, 0, 0, mu ? nmu : 0);
@@ -336,6 +361,12 @@ void count3x_run(Ctx &ctx, const Graph &g, int kind, int nmu, uint64_t *hist, ui
             }
         }
         if (wscale) *wscale = weighted ? weight_scale(g, 3) : 0;
+        // (the schedule that the timings report is the last full count's)
+        ctx.t.probes = last.probes;
+        ctx.t.table_log2 = last.table_log2;
+        ctx.t.block = last.block;
+        ctx.t.group = last.group;
+        ctx.t.hash_load = last.hash_load;
         return;
     }
     const size_t woff = ((size_t)ncnt + 1 + 31) / 32 * 32;

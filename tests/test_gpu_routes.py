@@ -1,10 +1,12 @@
 """Which kernel counts: plain and weighted triangle counts on both sides of the
-lines in row length, bins and points. Each count is repeated by the other
-kernel and equals it bit for bit."""
+lines in row length, bins and points, restricted counts and 6-edge counts
+likewise. Each count is repeated by the other kernel and equals it bit for bit;
+a restricted count leaves the schedule of the last full count in the timings."""
 import numpy as np
 import pytest
 
 import synth
+from tests import test_gpu_restricted_paged as restricted
 
 pytestmark = pytest.mark.gpu
 
@@ -75,4 +77,65 @@ def test_full_counts(ctx, monkeypatch, capfd, case):
     monkeypatch.setenv("GS_PAGED", "0" if paged else "1")
     other, p = took_paged(ctx, capfd, count)
     assert p != paged and same(got, other)
+    g.free()
+
+
+# points, row, bins, mu bins (0: equilateral), weighted, anchored -> paged
+RESTRICTED = [
+    (45_000, 50, 10, 0, False, False, False),
+    (45_000, 75, 10, 0, False, False, True),
+    (45_000, 75, 10, 0, True, True, True),
+    (45_000, 75, 20, 0, False, False, False),
+    (45_000, 110, 20, 0, False, True, True),
+    (45_000, 110, 20, 0, True, False, False),
+    (45_000, 180, 20, 0, True, False, True),
+    (45_000, 180, 24, 0, True, False, False),
+    (45_000, 39, 10, 5, False, False, False),
+    (45_000, 50, 10, 5, False, False, True),
+    (45_000, 50, 16, 5, False, False, False),
+    (45_000, 90, 16, 5, False, False, True),
+    (45_000, 75, 20, 5, False, False, True),
+]
+
+
+@pytest.mark.parametrize("case", RESTRICTED, ids=lambda c: "-".join(map(str, c)))
+def test_restricted_counts(ctx, monkeypatch, capfd, case):
+    n, row, nb, nmu, weighted, anchored, paged = case
+    monkeypatch.setenv("GS_PLAN_LOG", "1")
+    x, box = catalogue(n, row, nb)
+    w = synth.uniform_values(n, 0.5, 1.0, 822) if weighted else None
+    g = ctx.build_graph(x, box, 0.0, RMAX, nb, weights=w, keep_coords=True)
+    an = (n // 5, n // 2) if anchored else None
+    count = lambda: (ctx.count_3pcf_mu(g, nmu, weighted=weighted, anchors=an) if nmu else
+                     ctx.count_3pcf_equilateral(g, weighted=weighted, anchors=an))
+    print("routes", case, g.info().n_edges, flush=True)
+    monkeypatch.setenv("GS_PAGED", "0")
+    ctx.count_3pcf(g, weighted=weighted)
+    kept = ctx.timings()
+    monkeypatch.delenv("GS_PAGED")
+    got, p = took_paged(ctx, capfd, count)
+    t = ctx.timings()
+    assert p == paged
+    for f in ("probes", "table_log2", "block", "group", "hash_load"):
+        assert getattr(t, f) == getattr(kept, f), f
+    monkeypatch.setenv("GS_PAGED", "0" if paged else "1")
+    other, p = took_paged(ctx, capfd, count)
+    assert p != paged and same(got, other)
+    g.free()
+
+
+@pytest.mark.parametrize("case", restricted.CASES, ids=[c[0] for c in restricted.CASES])
+def test_forced_restricted_routes(ctx, monkeypatch, capfd, case):
+    """GS_PAGED=1 sends every plain restricted count of these catalogues to the
+    paged kernel, except in the box of one cell (few labels of a cell are
+    neighbours, and the mu bins' separations wrap); 0 sends none."""
+    name, mk, L, rmax, nb, nmu, periodic = case
+    monkeypatch.setenv("GS_PLAN_LOG", "1")
+    g = ctx.build_graph(mk(), L, 0.0, rmax, nb, keep_coords=True, periodic=periodic)
+    for forced in ("1", "0"):
+        monkeypatch.setenv("GS_PAGED", forced)
+        print("forced", name, forced, flush=True)
+        e = took_paged(ctx, capfd, lambda: ctx.count_3pcf_equilateral(g))
+        m = took_paged(ctx, capfd, lambda: ctx.count_3pcf_mu(g, nmu))
+        assert e[1] == m[1] == (forced == "1" and name != "wraps")
     g.free()
