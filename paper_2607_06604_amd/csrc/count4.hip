@@ -1692,8 +1692,20 @@ void count4_run(Ctx &ctx, const Graph &g, const Count4Out &o, const gs_anchor_ra
         }
         return lo;
     };
+    // 6-edge counters in global memory (8 bins and more) set the pace once a
+    // hub has many cliques: the bitset kernel adds to them with full
+    // wavefronts, the adjacency-byte one as it finds cliques, 1.02 to 1.10
+    // times as slow on crowded rows (5000 to 300000 points) but 0.5 to 0.98 on
+    // sparse ones. 8 bins, uniform points: 0.73 at 12 entries a row (weighted
+    // 1.03), 1.06 at 15; uneven rows 0.87 at 8.6 (1.04), 1.00 at 9.6 (1.05),
+    // 1.06 at 11. 12 bins, whose counters meet less: 0.72 at 15 (1.00), 1.02
+    // at 20; uneven 0.71 at 9.6 (0.96), 0.89 at 11 (1.01), 1.02 at 17.
+    const double mean_row = g.n ? (double)g.n_edges / (double)g.n : 0.0;
+    const bool uneven = (double)maxdeg > 2.0 * mean_row + 30.0;
+    const double crowded = uneven ? (weighted ? 8.0 : 9.5) + (nb >= 10 ? 3.0 : 0.0)
+                                  : (weighted ? 11.0 : 14.0) + (nb >= 10 ? 5.0 : 0.0);
     const char *em = getenv("GS_MATRIX4");
-    const int matrix = em ? atoi(em) : 1;
+    const int matrix = em ? atoi(em) : six && var == 2 && mean_row >= crowded ? 0 : 1;
     const uint32_t half_lds = (uint32_t)ctx.max_lds / 2 / 1280 * 1280;
     const uint32_t d1 = matrix == 1 ? fits(512, o.kind == kParity4, half_lds) : 2;
     const uint32_t d2 = matrix ? std::max(d1, fits(1024, false, (uint32_t)ctx.max_lds)) : 2;

@@ -139,3 +139,35 @@ def test_forced_restricted_routes(ctx, monkeypatch, capfd, case):
         m = took_paged(ctx, capfd, lambda: ctx.count_3pcf_mu(g, nmu))
         assert e[1] == m[1] == (forced == "1" and name != "wraps")
     g.free()
+
+
+# points, row, bins, weighted -> adjacency bytes
+SIX = [
+    (6_000, 20, 7, False, True),
+    (6_000, 12, 8, False, True),
+    (6_000, 12, 8, True, False),
+    (6_000, 16, 8, False, False),
+    (6_000, 18, 10, False, True),
+    (6_000, 18, 10, True, False),
+]
+
+
+@pytest.mark.parametrize("case", SIX, ids=lambda c: "-".join(map(str, c)))
+def test_six_edge_counts(ctx, monkeypatch, capfd, case):
+    n, row, nb, weighted, by_bytes = case
+    monkeypatch.setenv("GS_PLAN_LOG", "1")
+    x, box = catalogue(n, row, nb)
+    w = synth.uniform_values(n, 0.5, 1.0, 822) if weighted else None
+    g = ctx.build_graph(x, box, 0.0, RMAX, nb, weights=w, keep_coords=True)
+    print("six", case, g.info().max_deg, flush=True)
+    out = []
+    for mode in (None, "0" if by_bytes else "1"):
+        if mode:
+            monkeypatch.setenv("GS_MATRIX4", mode)
+        capfd.readouterr()
+        out.append(ctx.count_4pcf_full(g, weighted=weighted))
+        assert ("count4m" in capfd.readouterr().err) == (by_bytes if mode is None else not by_bytes)
+    a, b = out
+    assert np.array_equal(a.hist, b.hist) and a.n_cliques == b.n_cliques
+    assert not weighted or np.array_equal(a.wsum, b.wsum)
+    g.free()
