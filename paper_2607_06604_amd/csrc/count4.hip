@@ -1676,8 +1676,8 @@ void count4_run(Ctx &ctx, const Graph &g, const Count4Out &o, const gs_anchor_ra
     if (o.kind != kParity4) BLOCK = 512;   // the other kinds are built for 512 lanes only
     // hubs by degree: [3, d1] and (d1, d2] go to the adjacency-byte kernel
     // (512 lanes in half a CU's LDS, 1024 lanes in all of it), larger ones to
-    // the bitset kernel (GS_MATRIX4=0: all of them, GS_MATRIX4=2: none to the
-    // 512-lane form, for tests)
+    // the bitset kernel (for tests GS_MATRIX4=0: all of them, 1: by degree
+    // whatever the rules below say, 2: so, but none to the 512-lane form)
     auto log2_of = [](uint32_t deg) {
         int l = 6;
         while ((1u << l) < 2 * deg) ++l;
@@ -1707,8 +1707,20 @@ void count4_run(Ctx &ctx, const Graph &g, const Count4Out &o, const gs_anchor_ra
     const char *em = getenv("GS_MATRIX4");
     const int matrix = em ? atoi(em) : six && var == 2 && mean_row >= crowded ? 0 : 1;
     const uint32_t half_lds = (uint32_t)ctx.max_lds / 2 / 1280 * 1280;
-    const uint32_t d1 = matrix == 1 ? fits(512, o.kind == kParity4, half_lds) : 2;
-    const uint32_t d2 = matrix ? std::max(d1, fits(1024, false, (uint32_t)ctx.max_lds)) : 2;
+    uint32_t d1 = matrix == 1 ? fits(512, o.kind == kParity4, half_lds) : 2;
+    uint32_t d2 = matrix ? std::max(d1, fits(1024, false, (uint32_t)ctx.max_lds)) : 2;
+    // Each class is a launch that ends with its last hub, so few hubs take one
+    // kernel: the bitset one if it must take some (256 CUs; parity 1.4 to 1.9
+    // times its time in classes on 800 and 1500 points, 1.0 to 1.4 on 2500,
+    // 0.9 to 1.05 on 4000, 0.8 to 0.96 on 6500; weighted and pixel counts up
+    // to 1.25 on 4000, 0.82 to 1.16 on 6500, 0.66 to 0.98 on 10000; 6-edge
+    // 1.17 on 800, 0.87 to 1.21 on 1500, weighted 1.1 to 1.3, 0.78 to 1.1 on
+    // 2500), and on 800 points also for the 1024-lane class of a parity count
+    // (1.01 to 1.18).
+    const uint64_t per_cu = six ? 10 : o.kind == kParity4 && !weighted ? 16 : 26;
+    if (!em && ((maxdeg > d2 && (uint64_t)g.n < per_cu * ctx.n_cu) ||
+                (o.kind == kParity4 && maxdeg > d1 && (uint64_t)g.n < 4ull * ctx.n_cu)))
+        d1 = d2 = 2;
     Layout4 L = layout4(BLOCK, H, maxdeg, W, lds_cnt, nb, anchored, o.kind, weighted, tab6);
     if ((int)L.total > ctx.max_lds)
         fail(GS_EUNSUPPORTED, "4-clique kernel LDS footprint too large (forward degree " +

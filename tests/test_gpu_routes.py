@@ -171,3 +171,46 @@ def test_six_edge_counts(ctx, monkeypatch, capfd, case):
     assert np.array_equal(a.hist, b.hist) and a.n_cliques == b.n_cliques
     assert not weighted or np.array_equal(a.wsum, b.wsum)
     g.free()
+
+
+# crowd, points in all, kind, bins, weighted -> adjacency bytes take part
+CLASSES = [
+    (470, 3_470, "parity", 8, False, False),
+    (470, 4_500, "parity", 8, False, True),
+    (470, 4_500, "parity", 8, True, False),
+    (300, 900, "parity", 8, False, False),
+    (300, 900, "pixel", 8, False, True),
+    (600, 1_200, "six", 4, False, False),
+    (470, 6_000, "pixel", 8, False, False),
+    (600, 2_400, "six", 4, True, False),
+    (600, 2_800, "six", 4, False, True),
+]
+
+
+@pytest.mark.parametrize("case", CLASSES, ids=lambda c: "-".join(map(str, c)))
+def test_degree_classes(ctx, monkeypatch, capfd, case):
+    """Few hubs take one kernel, more are split by degree; both equal each
+    kernel on its own (GS_MATRIX4=0) and the forced split (1)."""
+    crowd, n, kind, nb, weighted, split = case
+    monkeypatch.setenv("GS_PLAN_LOG", "1")
+    box = 100.0
+    x = np.concatenate([np.mod(50.0 + 4.0 * (synth.uniform(crowd, 1.0, 823) - 0.5), box), synth.uniform(n - crowd, box, 824)])
+    w = synth.uniform_values(n, 0.5, 1.0, 825) if weighted else None
+    g = ctx.build_graph(x, box, 0.0, RMAX, nb, weights=w, keep_coords=True)
+    assert g.info().max_deg >= crowd - 1
+    print("classes", case, g.info().max_deg, flush=True)
+    out = []
+    for mode in (None, "0", "1"):
+        if mode:
+            monkeypatch.setenv("GS_MATRIX4", mode)
+        capfd.readouterr()
+        if kind == "six":
+            r = ctx.count_4pcf_full(g, weighted=weighted)
+            vals = [r.hist, r.n_cliques]
+        else:
+            r = ctx.count_4pcf_pixel(g) if kind == "pixel" else ctx.count_4pcf_parity(g, weighted=weighted)
+            vals = [r.even, r.pos, r.neg, r.n_cliques]
+        out.append(vals + ([r.wsum] if weighted else []))
+        assert ("count4m" in capfd.readouterr().err) == (split if mode is None else mode == "1")
+    assert all(np.array_equal(a, b) for o in out[1:] for a, b in zip(out[0], o))
+    g.free()
