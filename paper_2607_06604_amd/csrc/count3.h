@@ -106,6 +106,7 @@ struct Shape3 {
     double cell_points = 0;  // points per cell of the build's grid
     uint64_t max_rows = 0;   // entries that the spoke rows of one launch span
     int nmu = 0;             // mu bins (else 0)
+    uint64_t batch = 0;      // points of all catalogues of a batch (else 0)
 };
 
 // The schedule for a graph of that shape, or false where the paged table does

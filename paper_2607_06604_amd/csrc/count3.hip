@@ -1249,6 +1249,7 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
     shape.maxdeg = maxdeg;
     shape.nb = nb;
     shape.n = max_n;
+    shape.batch = nvirt;
     shape.mean_row = mean_row;
     for (int g = 0; g < ng; ++g)   // points per cell, averaged over the points
         shape.cell_points += gs[g]->cell_points * ((double)gs[g]->n / (double)std::max<uint64_t>(nvirt, 1));

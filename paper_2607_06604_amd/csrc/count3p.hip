@@ -1170,7 +1170,12 @@ namespace {
 // 55, 0.88 at 75; 18 bins weighted 1.61, 1.23 and 0.95; 24 bins 1.49, 1.33
 // and 1.20 at 85 (0.87 at 110), weighted 0.94 at 28 (the hash walk then has
 // one work group per CU), weighted and anchored 1.41 at 36, 0.94 at 75.
+// Batches: up to 18 bins 0.51 to 1.02 at 4 entries and more (2 to 32
+// catalogues of 2000 to 120000 points); 20 to 24 bins the same below 50000
+// points in all, beyond it 1.02 to 1.65 below 30 entries, 0.84 to 1.21 at 45,
+// 0.81 to 1.01 at 60.
 double least_row(const Shape3 &g) {
+    if (g.batch) return g.nb <= 18 || g.batch < 50000 ? 0.0 : 60.0;
     if (g.n < 24000 && !(g.weighted && g.nb > 17)) {
         if (!g.anchored || g.n < 5000) return 0.0;
         const bool uneven = (double)g.maxdeg > 2.0 * g.mean_row + 12.0;

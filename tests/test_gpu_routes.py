@@ -214,3 +214,26 @@ def test_degree_classes(ctx, monkeypatch, capfd, case):
         assert ("count4m" in capfd.readouterr().err) == (split if mode is None else mode == "1")
     assert all(np.array_equal(a, b) for o in out[1:] for a, b in zip(out[0], o))
     g.free()
+
+
+# catalogues, points each, row, bins -> paged
+BATCHES = [(2, 8_000, 8, 20, True), (8, 8_000, 8, 20, False), (8, 8_000, 8, 18, True), (2, 30_000, 8, 18, True),
+           (2, 30_000, 50, 20, False), (2, 30_000, 70, 20, True)]
+
+
+@pytest.mark.parametrize("case", BATCHES, ids=lambda c: "-".join(map(str, c)))
+def test_batches(ctx, monkeypatch, capfd, case):
+    count, n, row, nb, paged = case
+    monkeypatch.setenv("GS_PLAN_LOG", "1")
+    gs = []
+    for k in range(count):
+        x, box = catalogue(n, row, nb, 830 + k)
+        gs.append(ctx.build_graph(x, box, 0.0, RMAX, nb))
+    print("batch", case, flush=True)
+    got, p = took_paged(ctx, capfd, lambda: ctx.count_3pcf_batch(gs))
+    assert p == paged
+    monkeypatch.setenv("GS_PAGED", "0" if paged else "1")
+    other, p = took_paged(ctx, capfd, lambda: ctx.count_3pcf_batch(gs))
+    assert p != paged and all(np.array_equal(a.hist, b.hist) and a.n_triangles == b.n_triangles for a, b in zip(got, other))
+    for g in gs:
+        g.free()
