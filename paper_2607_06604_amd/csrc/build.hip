@@ -772,7 +772,14 @@ void build_end(Ctx &ctx, Graph &g, BuildJob &job, bool tile_ok) {
     if (const char *ew = getenv("GS_WINDOWS")) W = std::max(1, atoi(ew));
     if (W == 1 && tile_ok && fixed + csr > ctx.budget) {
         if (ctx.budget <= fixed + (1u << 20)) fail(GS_EDEVMEM, "budget below the graph's per-point arrays");
-        const uint64_t per_win = (ctx.budget - fixed) / 4;  // 4 window buffers while counting
+        // 4 window buffers while counting, and the count's packed hub rows
+        // (a window exceeds its share by up to a row and the windows' count)
+        // unless they would take much of it
+        uint64_t room = ctx.budget - fixed;
+        uint64_t rows = count3_row_bytes(ctx, g);
+        if (rows) rows += 20 * ((uint64_t)g.max_deg + 4096);
+        if (rows <= room / 4) room -= rows;
+        const uint64_t per_win = room / 4;
         W = (int)std::min<uint64_t>((csr + per_win - 1) / per_win, 1u << 20);
     }
     if (W > 1 && (uint64_t)W > (uint64_t)n) W = (int)std::max<uint32_t>(1, n);

@@ -303,6 +303,9 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
 // Whether count3_run would take the paged table for such a count (nmu: mu
 // bins; those counts have no other path there).
 bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nmu);
+// Device bytes beside the graph that a triangle count of it may take for
+// packed hub rows (long weighted or anchored rows; 0: none).
+uint64_t count3_row_bytes(const Ctx &ctx, const Graph &g);
 // Time schedules on a sample of g's hubs and keep the fastest for g's shape.
 void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out);
 // 4-clique counts. kind kParity4 (or kPixel4, parity from direction pixels):

@@ -94,6 +94,8 @@ struct PlanP {
     bool inorder = false;  // hubs go out one at a time in label order, not by tiles
     uint32_t tbytes = 0;   // bytes of the label table's pages
     uint32_t lds = 0;
+    uint32_t rowgroups = 0;  // work groups with a packed hub row (long weighted or anchored rows)
+    uint64_t rows = 0;       // and the device bytes of those rows
 };
 
 // What a schedule depends on.
@@ -107,6 +109,7 @@ struct Shape3 {
     uint64_t max_rows = 0;   // entries that the spoke rows of one launch span
     int nmu = 0;             // mu bins (else 0)
     uint64_t batch = 0;      // points of all catalogues of a batch (else 0)
+    uint64_t row_room = ~0ull;   // device bytes left for packed hub rows
 };
 
 // The schedule for a graph of that shape, or false where the paged table does

@@ -1334,7 +1334,7 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
 }
 
 namespace {
-Shape3 shape_of(const Graph &g, bool weighted, bool anchored, int nmu = 0) {
+Shape3 shape_of(const Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nmu = 0) {
     Shape3 h;
     h.maxdeg = g.max_deg;
     h.nb = g.nbins;
@@ -1346,10 +1346,24 @@ Shape3 shape_of(const Graph &g, bool weighted, bool anchored, int nmu = 0) {
     h.max_rows = g.n_edges;
     for (int w = 0; g.n_windows > 1 && w < g.n_windows; ++w)
         h.max_rows = std::max<uint64_t>(w ? h.max_rows : 1, g.win_edge[w + 1] - g.win_edge[w]);
+    // what the graph leaves of the budget (host-tiled: with its four window buffers)
+    const uint64_t held = g.device_bytes + (g.n_windows > 1 ? 20 * (h.max_rows + kRowSlack) : 0);
+    h.row_room = ctx.budget > held ? ctx.budget - held : 0;
     h.nmu = nmu;
     return h;
 }
 }  // namespace
+
+uint64_t count3_row_bytes(const Ctx &ctx, const Graph &g) {
+    uint64_t rows = 0;
+    for (bool anchored : {false, true}) {
+        Shape3 h = shape_of(ctx, g, (g.flags & GS_WEIGHTED) != 0, anchored);
+        h.row_room = ~0ull;
+        PlanP p;
+        if (planp(ctx, h, Tune3(), p)) rows = std::max(rows, p.rows);
+    }
+    return rows;
+}
 
 bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nmu) {
     if (g.n == 0 || g.n_windows != 1) return false;
@@ -1359,7 +1373,8 @@ bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nm
         if (weighted || anchored || wide_rows(g.n_edges)) return false;
         if (!(4.0 * g.rmax * (1.0 + 1e-9) < g.box && g.box <= 256.0 * g.rmax)) return false;
     }
-    const Shape3 h = shape_of(g, weighted, anchored, nmu);
+    const Shape3 h = shape_of(ctx, g, weighted, anchored, nmu);
+    if (nmu && h.row_room < 16 * h.n) return false;   // (the positions)
     const bool packed = h.n < (1ull << 24) - 1;
     PlanP p;
     return planp(ctx, h, tuned_for(ctx, tune_key(h.nb, weighted, packed, h.maxdeg, h.mean_row), kPaged3), p);
@@ -1372,7 +1387,7 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     const bool weighted = wsum != nullptr;
     const bool anchored = anchors != nullptr;
     if (anchored && (anchors->lo > anchors->hi)) fail(GS_EINVAL, "anchor range lo > hi");
-    const Shape3 shape = shape_of(g, weighted, anchored, nmu);
+    const Shape3 shape = shape_of(ctx, g, weighted, anchored, nmu);
     const uint32_t maxdeg = shape.maxdeg;
     const double mean_row = shape.mean_row;
     const bool packed = (uint64_t)g.n < (1ull << 24) - 1;
@@ -1662,7 +1677,7 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
     };
 
     // the built-in schedule, spelled out
-    const Shape3 shape = shape_of(g, weighted, false);
+    const Shape3 shape = shape_of(ctx, g, weighted, false);
     auto resolved = [&](const Tune3 &t, Tune3 &r) {   // the schedule that the paged kernel runs for t
         PlanP p;
         if (!planp(ctx, shape, t, p)) return false;

@@ -1213,7 +1213,7 @@ bool planp(const Ctx &ctx, const Shape3 &g, const Tune3 &tune, PlanP &p) {
     p.glog = mean_row >= 1000.0 ? 6 : mean_row >= 160.0 ? 5 : 4;
     if (tune.glog > 0 && !(far && tune.glog < 6)) p.glog = std::max(4, std::min(6, tune.glog));
     p.glog = env_int("GS_PGLOG", p.glog);
-    if (nmu) p.glog = std::min(p.glog, 5);
+    if (nmu || (g.row_room == 0 && (weighted || anchored))) p.glog = std::min(p.glog, 5);
     if (far && p.glog < 6) return false;
     p.kmax = tune.group > 0 ? std::min(tune.group, kMaxGroup) : kMaxGroup;
     p.kmax = p.glog >= 6 ? 1 : std::max(1, std::min(p.kmax, env_int("GS_GROUP", p.kmax)));
@@ -1263,6 +1263,19 @@ bool planp(const Ctx &ctx, const Shape3 &g, const Tune3 &tune, PlanP &p) {
     search(tune.block, tune.mode);
     if (best < 0) search(-1, -1);
     if (best < 0) return false;
+    p.rowgroups = 0;
+    p.rows = 0;
+    if (p.glog >= 6 && (weighted || anchored)) {
+        // packed hub rows, one per work group that can be resident; without
+        // the device memory for them, steps of 32 entries
+        p.rowgroups = (uint32_t)((size_t)ctx.n_cu * std::max<size_t>(1, std::min<size_t>(ctx.max_lds / p.lds, 2048 / p.block)) + kNumQueues);
+        p.rows = (uint64_t)p.rowgroups * maxdeg * (8 * weighted + 4 * anchored);
+        if (p.rows > g.row_room) {
+            Shape3 h = g;
+            h.row_room = 0;
+            return planp(ctx, h, tune, p);
+        }
+    }
     if (getenv("GS_PLAN_LOG"))
         fprintf(stderr, "count3p plan: maxdeg %u mean_row %.1f block %d glog %d mode %d group %d table %u lds %u waves/CU %d\n",
                 maxdeg, mean_row, p.block, p.glog, p.mode, p.kmax, p.tbytes, p.lds, best);
@@ -1276,14 +1289,11 @@ void launchp(Ctx &ctx, hipStream_t s, const C3Args &a0, const PlanP &P, bool wei
     a.mode = P.mode;
     a.kmax = P.kmax;
     a.group_cap = 2ull * P.block;
-    if (P.glog >= 6 && (weighted || anchored)) {
-        // packed hub rows, one per work group that can be resident
-        const size_t groups = (size_t)ctx.n_cu * std::max<size_t>(1, std::min<size_t>(ctx.max_lds / P.lds, 2048 / P.block)) + kNumQueues;
-        const size_t need = groups * a.maxdeg * 12;
-        if (rows.bytes < need) rows.alloc(need, ctx.pool);
+    if (P.rows) {
+        if (rows.bytes < P.rows) rows.alloc(P.rows, ctx.pool);
         a.wrow = rows.as<double>();
-        a.prow = (uint32_t *)(rows.as<double>() + groups * a.maxdeg);
-        a.rowgroups = (uint32_t)groups;
+        a.prow = (uint32_t *)(a.wrow + (weighted ? (size_t)P.rowgroups * a.maxdeg : 0));
+        a.rowgroups = P.rowgroups;
     }
     a.tbytes = P.tbytes;
     a.inorder = P.inorder;
