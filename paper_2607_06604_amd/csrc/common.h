@@ -354,7 +354,6 @@ void build_end(Ctx &ctx, Graph &g, BuildJob &job, bool tile_ok);
 struct Batch3 {
     DevBuf dv;          // device results + queues
     DevBuf gd;          // descriptors
-    DevBuf rows;        // (unused by unweighted counts)
     HostBuf hostdesc;   // staging of descriptors
     HostBuf hostcfg;    // staging of the configuration table
     HostBuf out;        // pinned results

@@ -1322,7 +1322,8 @@ void count3_batch_enqueue(Ctx &ctx, hipStream_t s, const Graph *const *gs, int n
         a.ntiles = tp.T();
     }
     if (nvirt > 0) {
-        if (paged) launchp(ctx, s, a, PP, false, false, true, false, b.rows);
+        DevBuf none;   // (unweighted counts pack no rows)
+        if (paged) launchp(ctx, s, a, PP, false, false, true, false, none);
         else if (P.block == 512) launch3_batch<512>(ctx, s, a, P);
         else if (P.block == 128) launch3_batch<128>(ctx, s, a, P);
         else launch3_batch<256>(ctx, s, a, P);
