@@ -458,7 +458,8 @@ int gs_compute_4pcf(gs_ctx *ctx, const gs_catalogue *data, const gs_catalogue *r
  *   nbins^3 configuration table and one LDS atomic (plus, weighted != 0,
  *   the weight gather, the exact triangle integer and two u64 LDS atomics).
  *   probe == 0 skips the hash (every candidate a hit): the LDS-atomic
- *   histogram ceiling at this bin count. block: 256 or 512 threads, or 768
+ *   histogram ceiling at this bin count, weighted with two u64 LDS atomics a
+ *   tuple and no other, as the paged table counts. block: 256 or 512 threads, or 768
  *   (weighted only, as weighted counts of long rows run).
  *   *per_s = candidates per second. nbins 1..24. */
 int gs_ceiling_copy(gs_ctx *ctx, uint64_t bytes, double *gbs);

@@ -5,8 +5,10 @@
 //  copy:  a device-to-device stream copy (16-byte loads and stores, grid
 //         stride): attainable HBM bandwidth, read + written bytes per second.
 //  hist:  one LDS atomic increment per tuple into C(nb+2,3) u32 counters
-//         through the ordered-triple configuration table (two more u64 LDS
-//         atomics per tuple when weighted): attainable binned tuples/s.
+//         through the ordered-triple configuration table; weighted, the
+//         exact term of the tuple's weights and its two u64 LDS atomics, as
+//         the paged triangle count adds it (count in the first word's upper
+//         bits): attainable binned tuples/s on evenly spread bins.
 //  probe: the per-candidate work of the triangle count's intersection
 //         (Sec. 3.1 done as hash probes): a coalesced 5-byte candidate load
 //         from an L2-resident array, the 24-bit hash, a linear-probe chain in
@@ -72,6 +74,7 @@ template <bool WEIGHTED> constexpr int ceil_unroll() { return WEIGHTED ? 6 : 4; 
 template <int BLOCK, bool PROBE, bool WEIGHTED>
 __global__ __launch_bounds__(BLOCK, BLOCK == 768 ? 6 : 1) void k_ceil_probe(CeilArgs a) {
     extern __shared__ __align__(16) unsigned char sm[];
+    constexpr bool WORDS = WEIGHTED && !PROBE;   // two words per counter, the count in the first
     const int nb = a.nb, n3 = nb * nb * nb;
     const uint32_t H = 1u << a.log2h, hmask = H - 1;
     uint16_t *lut = (uint16_t *)sm;
@@ -89,7 +92,8 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 768 ? 6 : 1) void k_ceil_probe(Ceil
     for (int t = tid; t < n3; t += BLOCK) {
         const int x = t / (nb * nb), y = (t / nb) % nb, z = t % nb;
         const int lo = min(x, min(y, z)), hi = max(x, max(y, z)), mid = x + y + z - lo - hi;
-        lut[t] = (uint16_t)(smb + o_hist + 4 * (rank_a(nb, lo) + rank_b(nb, mid) + hi));
+        const int c = rank_a(nb, lo) + rank_b(nb, mid) + hi;
+        lut[t] = (uint16_t)(smb + (WORDS ? o_wlo + 8 * c : o_hist + 4 * c));
     }
     for (int b = tid; b < a.nconf; b += BLOCK) {
         hist[b] = 0;
@@ -170,6 +174,8 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 768 ? 6 : 1) void k_ceil_probe(Ceil
                 yy[u] = v >> 26;
             }
         }
+        const double ws = WORDS ? a.w[xs] : 0.0;
+        const double plo = __dmul_rn(min_f64(hw, ws), a.wmul), phi = max_f64(hw, ws);   // the pair, ordered
         double wk[kCeilU];
 #pragma unroll
         for (int u = 0; u < kCeilU; ++u) wk[u] = (WEIGHTED && hit[u]) ? a.w[kk[u]] : 0.0;
@@ -177,6 +183,14 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 768 ? 6 : 1) void k_ceil_probe(Ceil
         for (int u = 0; u < kCeilU; ++u) {
             if (!hit[u]) continue;
             const uint32_t addr = lut[(xx[u] * (uint32_t)nb + yy[u]) * (uint32_t)nb + zz[u]];
+            if (WORDS) {
+                unsigned long long w0, w1;
+                term_words(__dmul_rn(__dmul_rn(plo, min_f64(wk[u], phi)), max_f64(wk[u], phi)), w0, w1);
+                __hip_atomic_fetch_add((lds_u64 *)(size_t)addr, w0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add((lds_u64 *)(size_t)(addr + 8 * a.nconf), w1, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                continue;
+            }
             __hip_atomic_fetch_add((lds_u32 *)(size_t)addr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (WEIGHTED) {
                 double p = hw, q = a.w[xx[u]], r = wk[u], t;

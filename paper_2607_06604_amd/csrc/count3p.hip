@@ -53,11 +53,6 @@ constexpr uint32_t kPages = 2 * kNP * kMaxGroup;   // LDS address of the first p
 static_assert(kPages == 1u << kMaxShift, "pages are aligned to their size");
 constexpr int kLane = 4;                 // entries per lane
 constexpr uint32_t kWaveSteps = 128;     // steps per fill of a wavefront's table
-constexpr int kCntShift = 42, kLowBits = 20;
-constexpr unsigned long long kLowMask = (1ull << kCntShift) - 1;
-constexpr double kRound = 0x1.8p72;                            // rounds a term to a multiple of 2^20
-constexpr unsigned long long kRoundBits = 0x4478000000000000ull;   // its bits
-constexpr double kBias = 0x1.8p52 + 0x1.0p19;                  // remainder + 2^19 in the low word
 
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32_a1 __attribute__((aligned(1)));
@@ -65,7 +60,6 @@ typedef __attribute__((address_space(1))) const u32x4_a4 gbl_u32x4;
 typedef __attribute__((address_space(1))) const u32_a1 gbl_u32u;
 typedef __attribute__((address_space(1))) const double gbl_f64;
 typedef __attribute__((address_space(3))) const uint8_t lds_u8;
-typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 
 constexpr int kMuLane = 2;         // triangles a lane takes at a time
 constexpr uint32_t kMuBuf = 64 * kMuLane + 256;   // triangles of a wavefront: those left over and 4 x 64 new ones
@@ -147,18 +141,6 @@ __device__ void flushp(const C3Args &a, const LayoutP &L, unsigned char *sm, uns
     if ((threadIdx.x & 63) == 0 && sum && tout) atomicAdd(tout, sum);
 }
 
-// Minimum and maximum of two numbers (no NaN here, so no canonicalisation).
-__device__ __forceinline__ double min_f64(double x, double y) {
-    double r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
-    return r;
-}
-__device__ __forceinline__ double max_f64(double x, double y) {
-    double r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
-    return r;
-}
-
 // A lane's value as a wavefront-uniform one.
 __device__ __forceinline__ uint64_t lane_u64(uint64_t x, int lane) {
     const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)x, lane);
@@ -200,10 +182,8 @@ __device__ __forceinline__ void add_term3(const WalkP &c, bool hit, uint32_t ad,
         wide = !narrow_term(t);
         if (ng) t = -t;
     }
-    const double up = __dadd_rn(t, kRound);
-    const double low = __dadd_rn(__dsub_rn(t, __dsub_rn(up, kRound)), kBias);
-    unsigned long long lw = (1ull << kCntShift) | (uint32_t)__double_as_longlong(low);
-    unsigned long long hw = (unsigned long long)__double_as_longlong(up);
+    unsigned long long lw, hw;
+    term_words(t, lw, hw);
     if (WT == 2 && wide) {   // only counted here: a zero term's words
         lw = (1ull << kCntShift) | (1ull << (kLowBits - 1));
         hw = kRoundBits;

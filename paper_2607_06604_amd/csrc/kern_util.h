@@ -16,6 +16,7 @@ __host__ __device__ inline uint32_t lds_align(uint32_t x, uint32_t a) { return (
 typedef __attribute__((address_space(1))) const uint32_t gbl_u32;
 typedef __attribute__((address_space(1))) const uint8_t gbl_u8;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 typedef __attribute__((address_space(3))) const uint16_t lds_u16;
 
 // Byte address of an LDS location.
@@ -220,6 +221,34 @@ __device__ __forceinline__ bool next_hub_run(uint32_t *queue, uint32_t h0, uint3
     if (v == kEmptyKey) return false;
     c.cur = v;  // hand the first hub of the new run back
     return true;
+}
+
+// The two 64-bit LDS counter words of a weighted triangle count (how they are
+// made and taken apart again: count3p.hip).
+constexpr int kCntShift = 42, kLowBits = 20;
+constexpr unsigned long long kLowMask = (1ull << kCntShift) - 1;
+constexpr double kRound = 0x1.8p72;                            // rounds a term to a multiple of 2^20
+constexpr unsigned long long kRoundBits = 0x4478000000000000ull;   // its bits
+constexpr double kBias = 0x1.8p52 + 0x1.0p19;                  // remainder + 2^19 in the low word
+
+// Minimum and maximum of two numbers (no NaN here, so no canonicalisation).
+__device__ __forceinline__ double min_f64(double x, double y) {
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+__device__ __forceinline__ double max_f64(double x, double y) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+    return r;
+}
+
+// What a term t (an integer of magnitude below 2^63) adds to them.
+__device__ __forceinline__ void term_words(double t, unsigned long long &lw, unsigned long long &hw) {
+    const double up = __dadd_rn(t, kRound);
+    const double low = __dadd_rn(__dsub_rn(t, __dsub_rn(up, kRound)), kBias);
+    lw = (1ull << kCntShift) | (uint32_t)__double_as_longlong(low);
+    hw = (unsigned long long)__double_as_longlong(up);
 }
 
 }  // namespace gsn
