@@ -17,8 +17,9 @@ stream of 256 catalogues.
 
 Rooflines. The triangle count looks candidates up in a label table in LDS and
 adds its hits to counters in LDS, so its roofline is triangles per second
-against the attainable rate of those additions alone, which the library's
-microbenchmark measures on this GPU for the same bin count and weighting.
+against the attainable rate of those additions alone (weighted: with the exact
+terms they add), which the library's microbenchmark measures on this GPU for
+the same bin count and weighting on evenly spread bins.
 Where the schedule is the hash table's (rows that the label table does not
 serve), it is candidates probed per second against the measured probe rate
 for the same table size, load, bin count, hit rate and weighting. The HBM
@@ -67,22 +68,24 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def kernel_source_digest(kind: str) -> str:
-    name = "count4.hip" if kind == "4pcf" else "count3.hip"
-    p = os.path.join(ROOT, "paper_2607_06604_amd", "csrc", name)
+KERNEL_SOURCE = {"k_count3": "count3.hip", "k_count3p": "count3p.hip", "k_count4m": "count4.hip"}
+
+
+def kernel_source_digest(kernel: str) -> str:
+    p = os.path.join(ROOT, "paper_2607_06604_amd", "csrc", KERNEL_SOURCE[kernel])
     with open(p, "rb") as f:
         return hashlib.sha256(f.read()).hexdigest()[:16]
 
 
-def stored_traffic(workload: str, kind: str):
+def stored_traffic(workload: str, kernel: str):
     """HBM bytes per launch from committed rocprofv3 counter runs, if they
-    were taken on the current kernel source (else None)."""
+    were taken on this kernel and its current source (else None)."""
     p = os.path.join(PROFILES, "traffic_%s.json" % workload)
     if not os.path.exists(p):
         return None
     with open(p) as f:
         d = json.load(f)
-    if d.get("kernel_source_sha256_16") != kernel_source_digest(kind):
+    if d.get("kernel") != kernel or d.get("kernel_source_sha256_16") != kernel_source_digest(kernel):
         return None
     return d.get("hbm_bytes_per_launch")
 
@@ -203,13 +206,14 @@ def run_workload(gsn, ctx, name, steps, warmup, tune=True, windows=0, with_cpu=T
     g.free()
     avg_launch_ms = kern_ms / max(launches, 1)
     count_kernel_ms = kern_ms / steps          # all launches of one count
-    traffic = stored_traffic(name, kind) if windows <= 1 else None
+    kernel = "k_count4m" if kind == "4pcf" else "k_count3p" if int(t.table_log2) == 0 else "k_count3"
+    traffic = stored_traffic(name, kernel) if windows <= 1 else None
 
     if kind == "4pcf":
         ops = FP64_OPS_PER_CLIQUE * tuples
         tflops = ops / (count_kernel_ms / 1e3) / 1e12 if count_kernel_ms > 0 else 0.0
         roofline = {"bound": "alu", "achieved": round(tflops, 3), "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
-                    "frac": round(tflops / FP64_PEAK_TFLOPS, 4), "traffic": traffic, "kernel": "k_count4m",
+                    "frac": round(tflops / FP64_PEAK_TFLOPS, 4), "traffic": traffic, "kernel": kernel,
                     "fp64_ops_per_clique": FP64_OPS_PER_CLIQUE, "avg_launch_ms": round(avg_launch_ms, 4),
                     "hbm_measured_GBs": round(traffic / (avg_launch_ms / 1e3) / 1e9, 1) if traffic else None}
     else:
@@ -233,13 +237,14 @@ def run_workload(gsn, ctx, name, steps, warmup, tune=True, windows=0, with_cpu=T
                    "frac_of_copy": round(gbs / ceil["copy_GBs"], 4) if ceil else None}
         if paged:
             rate = {"bound": "lds", "achieved": round(tri_rate, 2), "peak": round(hist_peak, 2), "unit": "Gtuples/s",
-                    "frac": round(tri_rate / hist_peak, 4) if hist_peak > 0 else None, "kernel": "k_count3p",
+                    "frac": round(tri_rate / hist_peak, 4) if hist_peak > 0 else None, "kernel": kernel,
                     "Gcandidates_per_s": round(achieved, 2),
-                    "peak_source": "gs_ceiling_probe: counter additions only, %d bins, %s, %d threads per group"
-                                   % (w.nbins, "weighted" if weighted else "unweighted", block)}
+                    "peak_source": "gs_ceiling_probe: counter additions%s only, evenly spread over %d bins, "
+                                   "%d threads per group"
+                                   % (" and exact weight terms" if weighted else "", w.nbins, block)}
         else:
             rate = {"bound": "alu", "achieved": round(achieved, 2), "peak": round(peak, 2), "unit": "Gprobe/s",
-                    "frac": round(achieved / peak, 4) if peak > 0 else None, "kernel": "k_count3",
+                    "frac": round(achieved / peak, 4) if peak > 0 else None, "kernel": kernel,
                     "peak_source": "gs_ceiling_probe: table 2^%d slots, %d keys, %d bins, hit rate %.3f, %s, "
                                    "%d threads per group" % (log2h, keys, w.nbins, hit,
                                                              "weighted" if weighted else "unweighted", block)}
