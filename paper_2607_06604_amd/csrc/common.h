@@ -299,9 +299,9 @@ __host__ __device__ inline int rank_b(int nb, int b2) { return (int)(-c2(nb - b2
 // built-in one.
 void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64_t *ntri,
                 const gs_anchor_range *anchors, const Tune3 *force = nullptr, uint32_t sample_lo = 0,
-                uint32_t sample_hi = 0, int nmu = 0);
-// Whether count3_run would take the paged table for such a count (nmu: mu
-// bins; those counts have no other path there).
+                uint32_t sample_hi = 0, int nmu = 0, bool restricted = false);
+// Whether count3_run would take the paged table for such a restricted count
+// (nmu: mu bins; those counts have no other path there).
 bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nmu);
 // Device bytes beside the graph that a triangle count of it may take for
 // packed hub rows (long weighted or anchored rows; 0: none).

@@ -85,6 +85,9 @@ constexpr int kMaxGroup = 4;             // hubs per group: two bits in a step e
 // configurations when the counters are flushed (kCube, unweighted only).
 enum { kRank = 0, kLut = 1, kCube = 2 };
 
+// Paged counts of fewer hubs leave out the tile plan where it does not pay.
+constexpr uint32_t kTileHubs = 12288;
+
 // The schedule of a paged-table count (count3p.hip).
 struct PlanP {
     int block = 256;
@@ -108,6 +111,7 @@ struct Shape3 {
     double cell_points = 0;  // points per cell of the build's grid
     uint64_t max_rows = 0;   // entries that the spoke rows of one launch span
     int nmu = 0;             // mu bins (else 0)
+    bool restricted = false; // for an equilateral or mu count
     uint64_t batch = 0;      // points of all catalogues of a batch (else 0)
     uint64_t row_room = ~0ull;   // device bytes left for packed hub rows
 };

@@ -1374,7 +1374,8 @@ bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nm
         if (weighted || anchored || wide_rows(g.n_edges)) return false;
         if (!(4.0 * g.rmax * (1.0 + 1e-9) < g.box && g.box <= 256.0 * g.rmax)) return false;
     }
-    const Shape3 h = shape_of(ctx, g, weighted, anchored, nmu);
+    Shape3 h = shape_of(ctx, g, weighted, anchored, nmu);
+    h.restricted = true;
     if (nmu && h.row_room < 16 * h.n) return false;   // (the positions)
     const bool packed = h.n < (1ull << 24) - 1;
     PlanP p;
@@ -1382,13 +1383,15 @@ bool count3_paged(Ctx &ctx, const Graph &g, bool weighted, bool anchored, int nm
 }
 
 void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64_t *ntri,
-                const gs_anchor_range *anchors, const Tune3 *force, uint32_t sample_lo, uint32_t sample_hi, int nmu) {
+                const gs_anchor_range *anchors, const Tune3 *force, uint32_t sample_lo, uint32_t sample_hi, int nmu,
+                bool restricted) {
     const int nb = g.nbins;
     const int nconf = (int)n_configs(nb) * std::max(1, nmu);
     const bool weighted = wsum != nullptr;
     const bool anchored = anchors != nullptr;
     if (anchored && (anchors->lo > anchors->hi)) fail(GS_EINVAL, "anchor range lo > hi");
-    const Shape3 shape = shape_of(ctx, g, weighted, anchored, nmu);
+    Shape3 shape = shape_of(ctx, g, weighted, anchored, nmu);
+    shape.restricted = restricted;
     const uint32_t maxdeg = shape.maxdeg;
     const double mean_row = shape.mean_row;
     const bool packed = (uint64_t)g.n < (1ull << 24) - 1;
@@ -1493,16 +1496,21 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
             a.h1 = std::min<uint32_t>(sample_hi, (uint32_t)g.n);
         }
         a.queue = queues;
-        // (few hubs: the three tile kernels cost more than the balance gains.
+        // Few hubs: the three tile kernels cost more than the balance gains.
         // Without tiles and with, as multiples of the hash walk's time, which
         // has them: 2000 points 0.58 and 0.74, clustered 0.62 and 0.85; 3500:
         // 0.72 and 0.77, 0.75 and 0.86; 8000: 0.91 and 0.75, 0.87 and 0.85,
         // and worst, at 2 to 10 entries a row, 1.24 and 1.08. Between, the row
         // decides: 5000 points of 5 entries 0.95 and 0.81, clustered 0.88 and
-        // 0.87, of 40 entries 0.69 and 0.64, clustered 0.72 and 0.82; 1.13
-        // against 1.38 ms for an estimate on 3000 + 3000 points)
+        // 0.87, of 40 entries 0.69 and 0.64, clustered 0.72 and 0.82. A few
+        // crowds among sparse hubs make tiles that one group works off alone:
+        // 9000 points of 11.6 entries, up to 89, 124 and 316 us (150 and 370
+        // weighted); evenly clustered ones, 19.7 entries up to 66, 125 and 102.
         const uint32_t hubs = a.h1 - a.h0;
-        if (use_tiles && !(paged && (hubs < 5000 || (hubs < 8000 && mean_row >= 30.0)))) {
+        const bool crowds = (double)maxdeg > 3.0 * mean_row + 12.0;
+        const bool uneven = (double)maxdeg > 2.0 * mean_row + 12.0;
+        const bool balance = hubs >= kTileHubs || (hubs >= (mean_row < 30.0 && !uneven ? 5000u : 8000u) && !crowds);
+        if (use_tiles && (!paged || balance)) {
             const TilePlan t1 = tile_plan(ctx, a.h1 - a.h0);
             enqueue_tiles(s, t1, a.rp, nullptr, 0, a.h0, a.h1, hpre, ctot, tbounds);
             a.tiles = tbounds;

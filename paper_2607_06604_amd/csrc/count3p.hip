@@ -1138,13 +1138,17 @@ namespace {
 // and clustered catalogues (8e5 points: uniform).
 // Small counts are decided by their start: at 5 to 25 entries 0.72 to 0.79 on
 // 18000 and 22000 points (weighted and anchored up to 1.05, from 18 bins on
-// weighted up to 1.08), still 0.74 to 0.87 on 26000 and 32000, but weighted
-// and anchored ones up to 1.08 on 40000, and any up to 1.19 on 60000 to
-// 250000. Anchors leave few hubs to share that start: on 5000 points and more
-// 1.01 to 1.14 at 2 entries, 0.75 to 1.02 from 4 on, but where the rows are
-// uneven up to 1.10 at 8 to 10 (weighted 1.18 at 10, 1.10 at 12, 1.08 at 15).
-// Large counts: up to 17 bins 1.03 to 1.23 at 28 entries, 0.92 to 1.04 at 36;
-// anchored 1.35 and 1.18, 1.0 to 1.03 at 42. From 18 bins on the counters and
+// weighted 1.03 to 1.08 at 8 entries, 0.90 to 1.01 from 13 on), 0.74 to 0.87
+// on 26000 and 32000 (weighted or anchored 0.78 to 1.03), 0.72 to 0.92 on
+// 40000 (up to 1.08), but 1.03 to 1.19 on 60000 to 250000. Anchors leave few hubs to
+// share that start: on 5000 points and more 1.01 to 1.14 at 2 entries, 0.75
+// to 1.02 from 4 on, but where the rows are uneven up to 1.10 at 8 to 10
+// (weighted 1.18 at 10, 1.10 at 12, 1.08 at 15); a few crowds among many
+// sparse hubs keep the hash walk's tiles waiting (0.4 to 0.9 without them).
+// Restricted counts have another kernel to beat (paged_pays in count3x.hip).
+// Large counts: up to 17 bins 1.03 to 1.23 at 28 entries, 1.0 to 1.14 at 32,
+// 0.90 at 34.5 (crowds of 50), 0.92 to 1.04 at 36; anchored 1.35 at 28 and
+// 1.18 at 36, 1.0 to 1.03 at 42. From 18 bins on the counters and
 // their address table, which the hash walk has no more of, leave less room
 // for work groups than shorter rows would fill: 20 bins 1.40 at 28, 1.12 at
 // 55, 0.88 at 75; 18 bins weighted 1.61, 1.23 and 0.95; 24 bins 1.49, 1.33
@@ -1156,12 +1160,14 @@ namespace {
 // 0.81 to 1.01 at 60.
 double least_row(const Shape3 &g) {
     if (g.batch) return g.nb <= 18 || g.batch < 50000 ? 0.0 : 60.0;
-    if (g.n < 24000 && !(g.weighted && g.nb > 17)) {
-        if (!g.anchored || g.n < 5000) return 0.0;
-        const bool uneven = (double)g.maxdeg > 2.0 * g.mean_row + 12.0;
-        return !uneven ? 3.0 : g.weighted ? 16.0 : 11.0;
+    if (g.restricted) return 28.0;
+    if (g.n < (g.nb > 17 ? 24000u : g.weighted || g.anchored ? 32000u : 45000u)) {
+        const double many = g.weighted && g.nb > 17 ? 12.0 : 0.0;
+        const double deg = g.maxdeg, row = g.mean_row;
+        if (!g.anchored || g.n < 5000 || (g.n < kTileHubs && deg > 6.0 * row)) return many;
+        return std::max(many, deg <= 2.0 * row + 12.0 ? 3.0 : g.weighted ? 16.0 : 11.0);
     }
-    if (g.nb <= 17) return g.anchored ? 42.0 : 36.0;
+    if (g.nb <= 17) return g.anchored ? 42.0 : 34.0;
     if (g.nb <= 22) return 70.0;
     if (g.weighted) return g.anchored ? 70.0 : 36.0;
     return g.anchored ? 100.0 : 110.0;
@@ -1223,11 +1229,12 @@ bool planp(const Ctx &ctx, const Shape3 &g, const Tune3 &tune, PlanP &p) {
                     if (room < 1024 || (gr > 1 && (uint32_t)room < least)) continue;
                     const int waves = gr * blk / 64;
                     // on a tie the smaller group, but the larger where hubs are few
-                    // and long, so that the last ones end sooner: 700 entries, 16 bins,
-                    // weighted, 14.1 ms by 256 threads and 9.1 by 512 on 15000 points
-                    // (12.3 by the hash walk), 18.9 and 19.1 on 40000; 8 bins 67.6
-                    // and 77 on 150000
-                    if (waves > best || (waves == best && mean_row >= 500.0 && p.glog < 6 && g.n < 128ull * ctx.n_cu)) {
+                    // and long, so that the last ones end sooner: 512 threads take
+                    // 0.57 to 0.99 of the time of 256 at 200 to 460 entries on 9000
+                    // to 32000 points, which the hash walk beat by up to 1.13, 0.97
+                    // to 1.14 at 60 to 100; 0.6 to 0.7 at 500 to 1000 on 15000, but
+                    // 1.14 on 150000 (weighted, 8 bins)
+                    if (waves > best || (waves == best && mean_row >= 200.0 && p.glog < 6 && g.n < 128ull * ctx.n_cu)) {
                         best = waves;
                         p.block = blk;
                         p.mode = mode;

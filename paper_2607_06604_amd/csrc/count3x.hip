@@ -296,9 +296,10 @@ void launchx_k(Ctx &ctx, const XArgs &a, uint32_t lds, bool w, bool an) {
 // count. Times as multiples of this kernel's. An equilateral count takes the
 // whole paged count for its diagonal, with the exact term of every triangle
 // when weighted, where this kernel drops a candidate of another bin unprobed;
-// so the count must be large enough to outweigh the paged one's tables (3e6
-// edges: 0.88 at most on 6e4 points at 50 entries and 3e4 at 110, but 1.05 on
-// 6e4 at 35 and 15000 at 170 with 16 bins), and past 16 bins, where the paged
+// so the count must be large enough to outweigh the paged one's tables (2e6
+// edges, 6e4 points at 35 entries: 0.77 to 0.95 with 4 and 8 bins, 0.98 with
+// 12, 1.05 to 1.11 with 16; 3e6 edges, 6e4 points at 50 and 3e4 at 110
+// entries: 0.88 at most), and past 16 bins, where the paged
 // kernel's counters cost it work groups, rows long: 20 bins 1.08 at 35
 // entries on 3e5 points and 0.78 at 75, 24 bins 1.15 and 0.98; weighted 20
 // bins 1.50 at 35, 1.02 at 110, 0.87 at 170; weighted 24 bins 1.40 at 170,
@@ -316,7 +317,7 @@ bool paged_pays(const Graph &g, int nmu, bool weighted, bool anchored) {
         const int64_t lds = 4 * n_configs(nb) * nmu + 2 * (int64_t)nb * nb * nb;
         return g.n_edges >= 2000000 && (lds < 14000 || lds > 40000 || row >= 80.0);
     }
-    if (g.n_edges < 3000000) return false;
+    if (g.n_edges < (nb <= 10 ? 2000000u : 3000000u)) return false;
     return nb <= 16 || row >= (!weighted ? 100.0 : nb <= 22 ? 170.0 : 500.0);
 }
 
@@ -347,7 +348,7 @@ void count3x_run(Ctx &ctx, const Graph &g, int kind, int nmu, uint64_t *hist, ui
         const Timings last = ctx.t;
         const int nconf = (int)n_configs(nb);
         std::vector<uint64_t> h(mu ? 0 : nconf), w(weighted ? 2 * (size_t)nconf : 0);
-        count3_run(ctx, g, mu ? hist : h.data(), weighted ? w.data() : nullptr, ntri, anchors, nullptr, 0, 0, mu ? nmu : 0);
+        count3_run(ctx, g, mu ? hist : h.data(), weighted ? w.data() : nullptr, ntri, anchors, nullptr, 0, 0, mu ? nmu : 0, true);
         if (!mu) {   // the configurations (b, b, b)
             *ntri = 0;
             for (int b = 0; b < nb; ++b) {

@@ -43,15 +43,18 @@ def took_paged(ctx, capfd, count):
 FULL = [
     (20_000, 12, 10, False, False, True),
     (20_000, 12, 20, False, False, True),
-    (20_000, 12, 20, True, False, False),
+    (20_000, 10, 20, True, False, False),
+    (20_000, 15, 20, True, False, True),
     (20_000, 2.5, 10, False, True, False),
     (20_000, 2.5, 10, False, False, True),
     (20_000, 4, 10, True, True, True),
-    (30_000, 20, 10, False, False, False),
-    (30_000, 33, 10, False, False, False),
-    (30_000, 39, 10, False, False, True),
-    (30_000, 39, 10, False, True, False),
-    (30_000, 46, 10, True, True, True),
+    (40_000, 20, 10, False, False, True),
+    (40_000, 20, 10, True, False, False),
+    (50_000, 20, 10, False, False, False),
+    (50_000, 32, 10, False, False, False),
+    (50_000, 37, 10, False, False, True),
+    (50_000, 39, 10, False, True, False),
+    (50_000, 46, 10, True, True, True),
     (30_000, 60, 18, False, False, False),
     (30_000, 60, 20, True, False, False),
     (30_000, 76, 20, True, False, True),
@@ -82,7 +85,8 @@ def test_full_counts(ctx, monkeypatch, capfd, case):
 
 # points, row, bins, mu bins (0: equilateral), weighted, anchored -> paged
 RESTRICTED = [
-    (45_000, 50, 10, 0, False, False, False),
+    (45_000, 42, 10, 0, False, False, False),
+    (45_000, 55, 12, 0, False, False, False),
     (45_000, 75, 10, 0, False, False, True),
     (45_000, 75, 10, 0, True, True, True),
     (45_000, 75, 20, 0, False, False, False),
@@ -90,6 +94,8 @@ RESTRICTED = [
     (45_000, 110, 20, 0, True, False, False),
     (45_000, 180, 20, 0, True, False, True),
     (45_000, 180, 24, 0, True, False, False),
+    (120_000, 31, 10, 0, False, False, True),
+    (120_000, 31, 10, 5, False, False, True),
     (45_000, 39, 10, 5, False, False, False),
     (45_000, 50, 10, 5, False, False, True),
     (45_000, 50, 16, 5, False, False, False),
@@ -237,3 +243,23 @@ def test_batches(ctx, monkeypatch, capfd, case):
     assert p != paged and all(np.array_equal(a.hist, b.hist) and a.n_triangles == b.n_triangles for a, b in zip(got, other))
     for g in gs:
         g.free()
+
+
+# points, row, weighted -> threads per work group (the LDS plan ties)
+BLOCKS = [(15_000, 230, True, 512), (15_000, 180, True, 256), (36_000, 230, True, 256), (15_000, 600, False, 512)]
+
+
+@pytest.mark.parametrize("case", BLOCKS, ids=lambda c: "-".join(map(str, c)))
+def test_group_size_of_few_long_hubs(ctx, monkeypatch, case):
+    n, row, weighted, block = case
+    x, box = catalogue(n, row, 10)
+    w = synth.uniform_values(n, 0.5, 1.0, 826) if weighted else None
+    g = ctx.build_graph(x, box, 0.0, RMAX, 10, weights=w)
+    print("block", case, flush=True)
+    got = ctx.count_3pcf(g, weighted=weighted)
+    t = ctx.timings()
+    assert t.table_log2 == 0 and t.block == block
+    monkeypatch.setenv("GS_PBLOCK", "256" if block == 512 else "512")
+    other = ctx.count_3pcf(g, weighted=weighted)
+    assert ctx.timings().block != block and same(got, other)
+    g.free()
