@@ -1716,10 +1716,15 @@ void count4_run(Ctx &ctx, const Graph &g, const Count4Out &o, const gs_anchor_ra
     // to 1.25 on 4000, 0.82 to 1.16 on 6500, 0.66 to 0.98 on 10000; 6-edge
     // 1.17 on 800, 0.87 to 1.21 on 1500, weighted 1.1 to 1.3, 0.78 to 1.1 on
     // 2500), and on 800 points also for the 1024-lane class of a parity count
-    // (1.01 to 1.18).
+    // (1.01 to 1.18). So does a weighted parity count of one bin, or of up to
+    // four on rows of over 240: the weighted additions meet on few counters,
+    // and the last hubs wait for them (1.03 to 1.41 on 1100 and 2200 points of
+    // 38 to 72 entries a row, 0.82 to 0.94 on 5000).
+    const bool meet = o.kind == kParity4 && weighted && mean_row >= 30.0 && (nb == 1 || (nb <= 4 && maxdeg > 240));
     const uint64_t per_cu = six ? 10 : o.kind == kParity4 && !weighted ? 16 : 26;
     if (!em && ((maxdeg > d2 && (uint64_t)g.n < per_cu * ctx.n_cu) ||
-                (o.kind == kParity4 && maxdeg > d1 && (uint64_t)g.n < 4ull * ctx.n_cu)))
+                (o.kind == kParity4 && maxdeg > d1 && (uint64_t)g.n < 4ull * ctx.n_cu) ||
+                (meet && (uint64_t)g.n < 10ull * ctx.n_cu)))
         d1 = d2 = 2;
     Layout4 L = layout4(BLOCK, H, maxdeg, W, lds_cnt, nb, anchored, o.kind, weighted, tab6);
     if ((int)L.total > ctx.max_lds)

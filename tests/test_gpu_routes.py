@@ -186,6 +186,9 @@ CLASSES = [
     (470, 4_500, "parity", 8, True, False),
     (300, 900, "parity", 8, False, False),
     (300, 900, "pixel", 8, False, True),
+    (300, 1_500, "parity", 1, True, False),
+    (300, 1_500, "parity", 5, True, True),
+    (300, 3_000, "parity", 1, True, True),
     (600, 1_200, "six", 4, False, False),
     (470, 6_000, "pixel", 8, False, False),
     (600, 2_400, "six", 4, True, False),
