@@ -53,12 +53,13 @@ struct C3Args {
     double wmul;            // 2^wscale
     int wgen;               // some weight is negative or some term may reach 2^63
     uint64_t flush_limit;   // flush LDS counters before this many increments
+    int look;               // paged table: unless the fullest one shows that there is room (weighted)
     uint32_t *queue;        // kQueueWords words
     unsigned long long *hist;   // nconf
     unsigned long long *wsum;   // 2*nconf (lo, hi)
     unsigned long long *ntri;   // 1
-    unsigned long long *probes; // candidates probed (nullable)
-    uint32_t *flushes;      // paged table, nullable: flushes in mid-count; those the fullest counter put off
+    unsigned long long *probes; // candidates probed (nullable); then, paged table, flushes in mid-count
+                                // (low half) and those the fullest counter put off
     uint32_t *err;          // bit 1: LDS addressing
     uint64_t wspan;         // WIDE: entries a segment of spoke rows may span from its first row
     const uint16_t *cfg3;   // kLut / kCube: configuration index of ordered triple (x*nb + y)*nb + z

@@ -1450,7 +1450,6 @@ void count3_run(Ctx &ctx, const Graph &g, uint64_t *hist, uint64_t *wsum, uint64
     if (const char *es = getenv("GS_WIDE_SPAN")) a.wspan = std::max<uint64_t>(strtoull(es, nullptr, 10), 1);
     a.wspan = std::min<uint64_t>(kWideSpan, std::max<uint64_t>(a.wspan, (uint64_t)maxdeg + 1));
     a.probes = dv + 3 * (size_t)nconf + 2;
-    a.flushes = (uint32_t *)(dv + 3 * (size_t)nconf + 3);
     a.cfg3 = (const uint16_t *)(dv + coff);
     uint32_t *queues = (uint32_t *)(dv + qoff);
     uint32_t *tbounds = (uint32_t *)(dv + toff);

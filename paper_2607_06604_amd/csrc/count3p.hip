@@ -549,6 +549,7 @@ struct SharedP {
     uint32_t pages, next;         // pages taken; smallest label beyond the round
     uint32_t chunk, done;         // spoke chunks claimed; wavefronts out of chunks
     uint32_t need, top;           // a flush is due; the fullest counter
+    uint32_t flushes, put_off;    // flushes in mid-count; those the fullest counter put off
 };
 static_assert(sizeof(SharedP) <= 384, "LayoutP::misc");
 
@@ -697,6 +698,8 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
         S.acc = 0;
         S.need = 0;
         S.top = 0;
+        S.flushes = 0;
+        S.put_off = 0;
     }
     wave_lds_sync();
     if (wid == 0) form_group<WT, ANCHORED, BATCH>(a, S, S.G[0], smax);
@@ -1037,7 +1040,7 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
                     // the walked candidates bound every counter; the fullest
                     // one is a better bound
                     unsigned long long now = a.flush_limit;
-                    if (WT) {
+                    if (WT && a.look) {
                         uint32_t top = 0;
                         for (int b = tid; b < a.nconf; b += BLOCK)
                             top = max(top, (uint32_t)(((unsigned long long *)(sm + L.cnt))[b] >> kCntShift));
@@ -1050,9 +1053,9 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
                         flushp<BLOCK, WT, MODE>(a, L, sm, hout, tout);
                         now = 0;
                     }
-                    if (tid == 0 && a.flushes) atomicAdd(a.flushes + (full ? 0 : 1), 1u);
                     __syncthreads();
                     if (tid == 0) {
+                        ++*(full ? &S.flushes : &S.put_off);
                         S.acc = now;
                         S.need = 0;
                         S.top = 0;
@@ -1074,6 +1077,8 @@ __global__ __launch_bounds__(BLOCK, (WT && BLOCK < 768) || MU ? 4 : 6) void k_co
     flushp<BLOCK, WT, MODE>(a, L, sm, hout, tout);
     probed = wave_sum64(probed);
     if (lane == 0 && a.probes && probed) atomicAdd(a.probes, (unsigned long long)probed);
+    if (tid == 0 && a.probes && (S.flushes | S.put_off))
+        atomicAdd(a.probes + 1, S.flushes | (unsigned long long)S.put_off << 32);
 }
 
 template <int B, int WT, bool AN, bool BATCH, int MODE, bool WIDE, bool LONG, bool MU = false>
@@ -1147,13 +1152,17 @@ namespace {
 // sparse hubs keep the hash walk's tiles waiting (0.4 to 0.9 without them).
 // Restricted counts have another kernel to beat (paged_pays in count3x.hip).
 // Large counts: up to 17 bins 1.03 to 1.23 at 28 entries, 1.0 to 1.14 at 32,
-// 0.90 at 34.5 (crowds of 50), 0.92 to 1.04 at 36; anchored 1.35 at 28 and
-// 1.18 at 36, 1.0 to 1.03 at 42. From 18 bins on the counters and
+// 0.90 at 34.5 (crowds of 50), 0.92 to 1.04 at 36; weighted with up to 12
+// bins 0.80 to 1.0 at 30 to 32 on crowds, 0.99 to 1.09 on uniform points;
+// anchored 1.35 at 28 and 1.18 at 36, 1.0 to 1.03 at 42, weighted 1.17 to
+// 0.89 at 36 (0.9 at 35 to 40 where the rest is sparse). From 18 bins on the counters and
 // their address table, which the hash walk has no more of, leave less room
 // for work groups than shorter rows would fill: 20 bins 1.40 at 28, 1.12 at
-// 55, 0.88 at 75; 18 bins weighted 1.61, 1.23 and 0.95; 24 bins 1.49, 1.33
+// 55, 0.88 at 75; 18 bins weighted 1.61, 1.23 and 0.95 (plain 0.78 to 0.95
+// from 32 on, anchored 1.40 at 33, 1.13 at 51); 24 bins 1.49, 1.33
 // and 1.20 at 85 (0.87 at 110), weighted 0.94 at 28 (the hash walk then has
-// one work group per CU), weighted and anchored 1.41 at 36, 0.94 at 75.
+// one work group per CU), weighted and anchored 1.41 at 36, 0.94 at 75. On
+// 60000 points 20 bins 1.07 at 45, 0.93 to 1.03 at 55, 24 bins 0.95 at 64.
 // Batches: up to 18 bins 0.51 to 1.02 at 4 entries and more (2 to 32
 // catalogues of 2000 to 120000 points); 20 to 24 bins the same below 50000
 // points in all, beyond it 1.02 to 1.65 below 30 entries, 0.84 to 1.21 at 45,
@@ -1161,16 +1170,18 @@ namespace {
 double least_row(const Shape3 &g) {
     if (g.batch) return g.nb <= 18 || g.batch < 50000 ? 0.0 : 60.0;
     if (g.restricted) return 28.0;
-    if (g.n < (g.nb > 17 ? 24000u : g.weighted || g.anchored ? 32000u : 45000u)) {
+    const bool plain = !g.weighted && !g.anchored;
+    const bool few = g.nb <= 17 || (g.nb == 18 && plain);   // bins
+    if (g.n < (!few || g.anchored ? 24000u : g.weighted ? 32000u : 45000u)) {
         const double many = g.weighted && g.nb > 17 ? 12.0 : 0.0;
         const double deg = g.maxdeg, row = g.mean_row;
         if (!g.anchored || g.n < 5000 || (g.n < kTileHubs && deg > 6.0 * row)) return many;
         return std::max(many, deg <= 2.0 * row + 12.0 ? 3.0 : g.weighted ? 16.0 : 11.0);
     }
-    if (g.nb <= 17) return g.anchored ? 42.0 : 34.0;
-    if (g.nb <= 22) return 70.0;
+    if (few) return !g.anchored ? (g.weighted && g.nb <= 12 ? 29.0 : 34.0) : g.weighted ? 35.0 : 42.0;
+    if (g.nb <= 22) return g.n < 100000 ? 52.0 : 70.0;
     if (g.weighted) return g.anchored ? 70.0 : 36.0;
-    return g.anchored ? 100.0 : 110.0;
+    return g.n < 100000 ? 65.0 : g.anchored ? 100.0 : 110.0;
 }
 }  // namespace
 
@@ -1287,6 +1298,7 @@ void launchp(Ctx &ctx, hipStream_t s, const C3Args &a0, const PlanP &P, bool wei
     const int wt = !weighted ? 0 : a.wgen ? 2 : 1;
     // fields of the weighted counters (see the head of this file)
     if (wt) a.flush_limit = std::min<uint64_t>(a.flush_limit, wt == 1 ? 1ull << 21 : 1ull << 20);
+    a.look = env_int("GS_FLUSH_LOOK", 1);   // (0: always flush, for tests)
     // a chunk of spokes fits half the limit
     const uint64_t chunk = (a.maxdeg > 4096 ? 16ull : 64ull) * ((uint64_t)a.maxdeg + (1ull << P.glog));
     a.flush_limit = std::max<uint64_t>(a.flush_limit, 2 * chunk + 2);

@@ -306,16 +306,20 @@ void launchx_k(Ctx &ctx, const XArgs &a, uint32_t lds, bool w, bool an) {
 // 1.32 at 300, 0.86 at 600. (5e5 clustered points, 15 bins: 4.7 to 2.6 ms.)
 // Where it is taken so: 0.62 on average, weighted 0.77, worst 0.96.
 // mu counts: 17.5 to 9.5 ms there with 5 mu bins; 0.75 at 35 entries on 6e4
-// points, 1.03 on 41000. While counters and address table together take 14
-// to 40 KB they cost the paged kernel work groups, this one none: 1.17 to
-// 1.36 at 35 entries, 1.0 to 1.16 at 50, 1.06 at 65, 0.90 at 80.
+// points, 1.03 on 41000. While counters and address table together take 14.5
+// to 40 KB they cost the paged kernel work groups, this one none: with 2 mu
+// bins 1.2 to 1.36 at 35 entries, 1.0 to 1.24 at 50, 1.06 at 65, 0.90 at 80;
+// with 5 and 10, where this kernel has more to work out, up to 27 KB 1.08 to
+// 1.30 at 35, 0.84 to 1.10 at 50, 0.97 at 65, beyond 0.92 to 1.15 at 35, 0.73
+// to 1.0 at 50.
 bool paged_pays(const Graph &g, int nmu, bool weighted, bool anchored) {
     const int nb = g.nbins;
     const double row = g.n ? (double)g.n_edges / (double)g.n : 0.0;
     if (g.n < 40000) return false;
     if (nmu) {
         const int64_t lds = 4 * n_configs(nb) * nmu + 2 * (int64_t)nb * nb * nb;
-        return g.n_edges >= 2000000 && (lds < 14000 || lds > 40000 || row >= 80.0);
+        const double least = lds < 14500 || lds > 40000 ? 28.0 : lds < 27000 ? (nmu < 4 ? 78.0 : 60.0) : nmu < 4 ? 70.0 : 42.0;
+        return g.n_edges >= 2000000 && row >= least;
     }
     if (g.n_edges < (nb <= 10 ? 2000000u : 3000000u)) return false;
     return nb <= 16 || row >= (!weighted ? 100.0 : nb <= 22 ? 170.0 : 500.0);

@@ -54,13 +54,17 @@ FULL = [
     (50_000, 32, 10, False, False, False),
     (50_000, 37, 10, False, False, True),
     (50_000, 39, 10, False, True, False),
-    (50_000, 46, 10, True, True, True),
-    (30_000, 60, 18, False, False, False),
-    (30_000, 60, 20, True, False, False),
-    (30_000, 76, 20, True, False, True),
-    (30_000, 76, 18, False, True, True),
-    (30_000, 90, 24, False, False, False),
-    (30_000, 120, 24, False, False, True),
+    (50_000, 37, 10, True, True, True),
+    (50_000, 31, 10, True, False, True),
+    (50_000, 31, 15, True, False, False),
+    (30_000, 40, 18, False, False, True),
+    (30_000, 48, 18, False, True, False),
+    (30_000, 48, 20, True, False, False),
+    (30_000, 56, 20, True, False, True),
+    (30_000, 56, 18, False, True, True),
+    (110_000, 60, 20, False, False, False),
+    (30_000, 60, 24, False, False, False),
+    (30_000, 70, 24, False, False, True),
     (30_000, 60, 24, True, True, False),
     (30_000, 60, 24, True, False, True),
 ]
@@ -99,7 +103,9 @@ RESTRICTED = [
     (45_000, 39, 10, 5, False, False, False),
     (45_000, 50, 10, 5, False, False, True),
     (45_000, 50, 16, 5, False, False, False),
-    (45_000, 90, 16, 5, False, False, True),
+    (45_000, 65, 16, 5, False, False, True),
+    (45_000, 65, 16, 2, False, False, False),
+    (60_000, 45, 15, 10, False, False, True),
     (45_000, 75, 20, 5, False, False, True),
 ]
 
