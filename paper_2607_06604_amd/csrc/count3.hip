@@ -1814,7 +1814,7 @@ void tune3(Ctx &ctx, const Graph &g, bool weighted, gs_plan3 *out) {
         out->group = cur.group;
         out->table = paged ? 128 : cur.tmax;
         out->counters = cur.mode;
-        out->hash_load = paged ? 0 : cur.hload;
+        out->hash_load = paged ? 5 : cur.hload;   // (no hash table)
         out->truncate = paged ? 1 : cur.trunc;
         out->trials = trials;
         out->sample_ms = best;
