@@ -310,7 +310,8 @@ typedef struct {
                          /* 2: per-(x,y,z) counters folded at flush              */
     int32_t hash_load;   /* hub hash table load bound: 5 (1/2) or 7 (0.7); 5 too  */
                          /* where the paged label table counts (no hash table,    */
-                         /* 128 step entries, rows always cut)                    */
+                         /* 128 step entries, rows always cut); the timings of    */
+                         /* a count name its kernel (table_log2 0: paged)         */
     int32_t truncate;    /* 1: spoke rows cut at the hub row's largest label     */
     int32_t trials;      /* schedules timed                                      */
     double sample_ms;    /* chosen schedule on the sample (kernel time)          */
